@@ -52,8 +52,8 @@ __device__ __forceinline__ float sum2_bf16(uint32_t w, float acc) {
                                          __builtin_bit_cast(bf16x2, 0x3f803f80u), acc, false);
 }
 
-// Buffer loads straight into LDS.  A raw buffer resource over memory starting at `base` (2 GiB
-// range, word 3 as gfx9 raw dword loads need); 16 bytes per lane from byte offset voff + soff
+// Buffer loads straight into LDS.  A raw buffer resource over `bytes` bytes of memory starting at
+// `base` (word 3 as gfx9 raw dword loads need; loads past the range return zeros); 16 bytes per lane from byte offset voff + soff
 // into LDS at l + 16 * lane (the LDS address is wave-uniform).  The builtins sit in device
 // functions of their own: inside a kernel body the host compilation would drop the kernel.
 // (Loads into LDS issued as global loads count on the LDS-read counter as well, and the
@@ -61,8 +61,9 @@ __device__ __forceinline__ float sum2_bf16(uint32_t w, float acc) {
 // not.)
 typedef __attribute__((address_space(3))) void lds_void_t;
 constexpr int kBufferWord3 = 0x00020000;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, kBufferWord3);
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base,
+                                                               uint32_t bytes = 0x7fffffff) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, kBufferWord3);
 }
 __device__ __forceinline__ void buffer_load_to_lds(__amdgpu_buffer_rsrc_t rs, void* l,
                                                    uint32_t voff, uint32_t soff) {

@@ -357,14 +357,13 @@ hipError_t launch_stream_rows(int n_rows, int hidden, int vocab, const void* h, 
 }
 
 // ---------------------------------------------------------------------------------------
-// Large-batch kernel: 256 (vocabulary) x 256 (positions) tiles.
+// Large-batch kernel: tiles of 256 vocabulary rows x up to 256 positions.
 //
 // Both operands go HBM/L2 -> LDS by buffer loads straight into LDS (lane l of a wave writes its
-// 16 bytes to LDS base + 16 l) into a ring of RING stages of BK = 32 hidden columns, RING - 1
-// stages in flight; no staging registers and no LDS store instructions.  LDS rows are 64 bytes
-// without padding; the 16-byte chunk c of row r is kept in slot c ^ ((r / 4) % 4), which makes
-// the 16-row MFMA operand reads (rows in the order rho of lmhead_tile_kernel) free of bank
-// conflicts.  Four waves form a 2 x 2 grid of 128 x 128 sub-tiles of 16x16x32 MFMA blocks.
+// 16 bytes to LDS base + 16 l), in stages of BK = 64 hidden columns; no staging registers and no
+// LDS store instructions.  LDS rows are 128 bytes without padding, their eight 16-byte chunks
+// permuted by row so that the 16-row MFMA operand reads (rows in the order rho of tile_run) are
+// free of bank conflicts.  Four waves form a 2 x 2 grid of sub-tiles of 16x16x32 MFMA blocks.
 //
 // Tile order is XCD-aware: the launch sequence takes vocabulary tiles in bands of kBand, each
 // band swept position tile by position tile, and is cut into one contiguous segment per XCD
@@ -374,9 +373,7 @@ hipError_t launch_stream_rows(int n_rows, int hidden, int vocab, const void* h, 
 constexpr int kXcds = 8;
 constexpr int kBand = 4;
 constexpr int kTileBM = 256;     // vocabulary rows per tile
-constexpr int kTileBN = 256;     // block positions per tile
-constexpr int kTileBK = 32;      // hidden columns per ring stage
-constexpr int kTileRing = 4;     // ring stages
+constexpr int kTileBK = 64;      // hidden columns per ring stage
 constexpr int kTileGroups = 256; // persistent workgroups (one per compute unit)
 
 int tile_vtiles(int vocab) { return (vocab + kTileBM - 1) / kTileBM; }
@@ -454,8 +451,7 @@ __device__ __forceinline__ void pair_sum_min(float& s, float& t, int32_t& idx) {
 // Statistics of one column of a wave's 16x16x32 accumulator tile: lane l holds, for column block
 // tn, vocabulary rows vbase + 16 tm + 4 r (tm < TM, r < 4; vbase includes the lane's l / 16) of
 // one column, and the four lanes l % 16 + 16 q together hold the column's 16 TM rows (the rows
-// of a 16-row block reach the MFMA in the order the fragment reads use, see
-// lmhead_tile_kernel).  A max pass in four chains (by r), the column maximum M over the four
+// of a 16-row block reach the MFMA in the order the fragment reads use, see tile_run).  A max pass in four chains (by r), the column maximum M over the four
 // lanes (pair_max), one exponential pass against M, then the four lanes' sums added pairwise in
 // registers (pair_sum_min): identical bits on all four lanes.  Each chain walks its rows in
 // decreasing order, so its last z == M is its lowest row; the argmax is kept as the block index
@@ -541,45 +537,242 @@ __device__ __forceinline__ void band_tile(int s, int n_vtiles, int n_rtiles, int
 }
 
 // Persistent form of the large-batch kernel: kTileGroups workgroups, one per compute unit, each
-// computing a sequence of 256 x 256 tiles (vocabulary rows x block positions).  The launch
+// computing a sequence of tiles of 256 vocabulary rows x BN = 32 TN block positions.  The launch
 // sequence is cut into 8 contiguous segments, one per XCD (workgroup g runs on XCD g % 8 and
 // takes every 32nd tile of its XCD's segment), so each XCD gets the same number of tiles and
 // its 32 resident workgroups share a few W and h tiles in its L2.  With fewer tiles than
 // workgroups, workgroup g computes tile g.
 //
-// Per tile: 4 waves form a 2 x 2 grid of 128 x 128 sub-tiles, each 8 x 8 blocks of 16x16x32 bf16
-// MFMAs (256 accumulator registers per lane).  A 32-column ring stage is one MFMA k step: per
-// stage a wave reads 16 fragments (16 KB) from LDS and issues 64 MFMAs.  Step kt: one barrier
-// (stage kt + 1 has landed, and every wave's reads of stage kt are done), then the 64 MFMAs of
-// stage kt from one register set while the fragments of stage kt + 1 go into the other and
-// stage kt + RING is loaded into the slot of stage kt; groups of six MFMAs carry one load into
-// LDS and two fragment reads, so both are spread over the step.  The ring slot of a stage is its
-// index in the workgroup's whole sequence modulo RING, so the last steps of a tile issue the
-// next tile's first stages and read its stage 0: its operands arrive while this tile finishes
-// and runs its epilogue.  Measured against 32x32x16 blocks (the same tiles and ring): 16x16x32
-// MFMAs sustain a higher clock under the chip's power limit.
-template <int BM, int RING, bool kTop2>
+// Per tile: 4 waves form a 2 x 2 grid of 128 x 16 TN sub-tiles, each 8 x TN blocks of 16x16x32
+// bf16 MFMAs (32 TN accumulator registers per lane).  A stage is 64 hidden columns, two MFMA k
+// steps a and b; per step a wave reads 8 + TN fragments (1 KB each) from LDS into one of two
+// register sets and issues 8 TN MFMAs from the other.  W stages go round three LDS slots, h
+// stages round two, 160 KB at TN = 8:
+//   step a of stage s: MFMAs of (s, a); reads the fragments of (s, b); loads W of stage s + 2 into
+//                      the slot that stage s - 1 left;
+//   barrier:           stage s + 1 has landed, and every wave's reads of stage s are done;
+//   step b of stage s: MFMAs of (s, b); reads the fragments of (s + 1, a); loads h of stage s + 2
+//                      into the slot that stage s left.
+// W, which comes from HBM, thus has three steps to land, h, which mostly comes from L2, two.
+// (Two slots for both: 870 us against 806 us for 1024 positions of a 126464 x 4096 head; a third
+// slot for h where it fits, TN <= 5, is no faster.)  The slots go on across tiles: the last two
+// stages of a tile load the next tile's first two and read its stage 0, so its operands arrive
+// while this tile finishes and runs its epilogue.  Measured against 32x32x16 blocks (the
+// same tiles): 16x16x32 MFMAs sustain a higher clock under the chip's power limit.
+//
+// Waves 0 and 1 load W (16 instructions of 1 KB per stage each), waves 2 and 3 load h (2 TN
+// each); the kernel body is instantiated per role (tile_run), because the wait counts are
+// immediates.
+constexpr int kTileTM = kTileBM / 32;  // 16-row blocks per wave
+
+template <int TN>
+struct TileShape {
+  static constexpr int BM = kTileBM, BN = 32 * TN, BK = kTileBK;
+  static constexpr int kRowB = BK * 2;  // 128 bytes per LDS row
+  static constexpr int kWSlot = BM * kRowB, kHSlot = BN * kRowB;
+  static constexpr int kH0 = 3 * kWSlot;  // the two h slots follow the three W slots
+  static constexpr int kLdsBytes = kH0 + 2 * kHSlot;
+};
+
+template <int TN, bool kTop2, bool kLoadsW>
+__device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restrict__ h,
+                                         const uint16_t* __restrict__ w, int n_rows, int hidden,
+                                         int vocab, int n_vtiles, int n_rtiles,
+                                         Partial* __restrict__ part, float* __restrict__ part2,
+                                         int s0, int step, int s_end, int wave) {
+  using Shape = TileShape<TN>;
+  constexpr int BM = Shape::BM, BN = Shape::BN, BK = Shape::BK, kRowB = Shape::kRowB;
+  constexpr int kWSlot = Shape::kWSlot, kHSlot = Shape::kHSlot, kH0 = Shape::kH0;
+  constexpr int WM = 2, TM = kTileTM;
+  constexpr int kWaveM = 16 * TM, kWaveN = 16 * TN;
+  constexpr int kReads = TM + TN, kMfmas = TM * TN;
+  constexpr int kInst = kLoadsW ? 2 * TM : 2 * TN;  // 1 KB load instructions per stage
+  static_assert(BK == 64, "two 16x16x32 k steps per stage");
+  static_assert(Shape::kLdsBytes <= 160 * 1024, "slots fit in LDS");
+  static_assert(BN * (sizeof(Partial) + 4) <= kWSlot, "reduction fits in a W slot");
+
+  const int lane = threadIdx.x & 63;
+  const int wm = wave % WM, wn = wave / WM;
+  const int q4 = lane >> 4, l16 = lane & 15;
+  const int ns = hidden / BK;  // stages per tile, >= 1
+  const bool chain = ns >= 2;  // the last stages of a tile load the next tile's first two
+
+  // Load instruction i of this wave covers rows 8 q .. 8 q + 7 of its operand, q = (wave % 2)
+  // kInst + i: lane L fetches one 16-byte chunk of row 8 q + L / 8 into LDS slot L % 8 of the
+  // row, so eight lanes read 128 contiguous bytes, a whole cache line in one L2 request.  (16
+  // rows x 64 bytes per instruction make twice the requests, and the L2 request rate then bounds
+  // the kernel.)  The loads are buffer loads into LDS: a resource per tile and operand in scalar
+  // registers, whose range ends with the operand's last row, so rows past the end read as zero
+  // without a clamp; a byte offset in a vector register, the same for every second instruction;
+  // and the instruction's rows and the stage's columns as the scalar offset.  (Global loads into
+  // LDS would count on the LDS-read counter as well, and the compiler then waits for every
+  // outstanding fragment read before each use of one.)
+  const int q0 = (wave & 1) * kInst;
+  // Chunk c of row r sits at place c ^ swz(r) of the LDS row: distinct over the rows that eight
+  // consecutive lanes of a fragment read touch.
+  auto swz = [](int r) { return ((r >> 2) & 3) | ((r & 1) << 2); };
+  const uint32_t row_bytes = static_cast<uint32_t>(hidden) * 2;
+  uint32_t voff[2];  // by the instruction's parity (swz depends on row mod 16)
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = 8 * i + (lane >> 3);
+    voff[i] = row * row_bytes + 16 * ((lane & 7) ^ swz(row));
+  }
+  auto source = [&](int vt_, int rt_) {
+    const uint16_t* base = kLoadsW ? w + static_cast<size_t>(vt_) * BM * hidden
+                                   : h + static_cast<size_t>(rt_) * BN * hidden;
+    const int rows = kLoadsW ? min(vocab - vt_ * BM, BM) : min(n_rows - rt_ * BN, BN);  // > 0
+    return make_rsrc(base, static_cast<uint32_t>(rows) * row_bytes);
+  };
+  // Load instruction i of stage `stage` of the tile described by rs, into the slot at `slot`.
+  auto load = [&](__amdgpu_buffer_rsrc_t rs, int stage, int slot, int i) {
+    buffer_load_to_lds(rs, smem + slot + (q0 + i) * 1024, voff[i & 1],
+                       stage * (BK * 2) + (q0 + (i & ~1)) * 8 * row_bytes);
+  };
+  // Fragment f of k step `half` of a stage (f < TM: W block f of this wave, else h block f - TM):
+  // lane l reads row rho(l % 16) = 4 (l % 4) + (l % 16) / 4 of the 16-row block, 16-byte chunk
+  // 4 half + l / 16 (k = 32 half + 8 (l / 16) .. + 7).  The MFMA then sees the block's rows
+  // permuted by rho, on both operands: accumulator register r of lane l holds vocabulary row
+  // 16 tm + rho(4 (l / 16) + r) = 16 tm + 4 r + l / 16 of the wave's W rows, for position
+  // tn * 16 + rho(l % 16) of its h rows.
+  const int rho = 4 * (l16 & 3) + (l16 >> 2);
+  auto frag = [&](int wslot, int hslot, int half, int f) {
+    const int r = f < TM ? wm * kWaveM + f * 16 + rho : wn * kWaveN + (f - TM) * 16 + rho;
+    return *reinterpret_cast<const bf16x8*>(smem + (f < TM ? wslot : hslot) + r * kRowB +
+                                            16 * ((4 * half + q4) ^ swz(r)));
+  };
+
+  // LDS offsets of the slots of the current stage and of the next ones, turned once per stage.
+  int w0 = 0, w1 = kWSlot, w2 = 2 * kWSlot;
+  int h0 = kH0, h1 = kH0 + kHSlot;
+  f32x4 acc[TM][TN];
+  int s = s0, vt, rt;
+  band_tile(s, n_vtiles, n_rtiles, vt, rt);
+  __amdgpu_buffer_rsrc_t src = source(vt, rt), nsrc = src;
+  // Stages 0 and 1 of a tile, then the fragments of (0, a).
+  bf16x8 xa[TM], xb[TN], ya[TM], yb[TN];
+  auto start = [&]() {
+#pragma unroll
+    for (int i = 0; i < kInst; ++i) load(src, 0, kLoadsW ? w0 : h0, i);
+#pragma unroll
+    for (int i = 0; i < kInst; ++i) load(src, min(1, ns - 1), kLoadsW ? w1 : h1, i);
+    wait_vm_lds_and_barrier<kInst>();  // stage 0 has landed
+#pragma unroll
+    for (int f = 0; f < TM; ++f) xa[f] = frag(w0, h0, 0, f);
+#pragma unroll
+    for (int f = 0; f < TN; ++f) xb[f] = frag(w0, h0, 0, TM + f);
+  };
+  start();
+  for (;;) {
+    const int nxt = s + step;
+    const bool next = nxt < s_end;
+    int nvt = 0, nrt = 0;
+    if (next) {
+      band_tile(nxt, n_vtiles, n_rtiles, nvt, nrt);
+      nsrc = source(nvt, nrt);
+    }
+    const bool pre = next && chain;
+
+    // One k step: the MFMAs from (ca, cb), the fragments of k step `half` of the stage in slots
+    // wslot / hslot into (na, nb), and with do_load stage `stage` of p into the slot at lslot;
+    // loads and fragment reads spread over the first three quarters of the MFMAs.
+    auto body = [&](int wslot, int hslot, int half, bool do_load, __amdgpu_buffer_rsrc_t p,
+                    int stage, int lslot, const bf16x8 (&ca)[TM], const bf16x8 (&cb)[TN],
+                    bf16x8 (&na)[TM], bf16x8 (&nb)[TN]) {
+      auto load_at = [](int l) { return (6 * l + 1) * kMfmas / (8 * kInst); };
+      auto read_at = [](int f) { return (6 * (f / 2) + 3 + 2 * (f & 1)) * kMfmas / (4 * kReads); };
+      int l = 0, f = 0;  // constants of the unrolled code
+#pragma unroll
+      for (int i = 0; i < kMfmas; ++i) {
+        mfma16_tied(acc[i / TN][i % TN], ca[i / TN], cb[i % TN]);
+        if (do_load && l < kInst && load_at(l) <= i) load(p, stage, lslot, l++);
+        if (f < kReads && read_at(f) <= i) {
+          if (f < TM)
+            na[f] = frag(wslot, hslot, half, f);
+          else
+            nb[f - TM] = frag(wslot, hslot, half, f);
+          ++f;
+        }
+      }
+      static_assert(kInst <= kMfmas * 7 / 8, "every load finds its MFMA");
+    };
+    // One stage; stage `stage` of p is loaded on the way.
+    auto run_stage = [&](__amdgpu_buffer_rsrc_t p, int stage) {
+      body(w0, h0, 1, kLoadsW, p, stage, w2, xa, xb, ya, yb);
+      // the next stage has landed (W: all but the stage just issued)
+      wait_vm_lds_and_barrier<kLoadsW ? kInst : 0>();
+      body(w1, h1, 0, !kLoadsW, p, stage, h0, ya, yb, xa, xb);
+      const int w_left = w0, h_left = h0;
+      w0 = w1;
+      w1 = w2;
+      w2 = w_left;
+      h0 = h1;
+      h1 = h_left;
+    };
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+      for (int b = 0; b < TN; ++b) acc[a][b] = f32x4{};
+    acc_fence_in(acc);  // the zeros are in place before the first MFMA reads them
+    // The last two stages load the next tile's first two (or, without a next tile or with one
+    // stage per tile, this tile's last stage again, never read).
+    int st = 0;
+    for (; st + 2 < ns; ++st) run_stage(src, st + 2);
+    const __amdgpu_buffer_rsrc_t tsrc = pre ? nsrc : src;
+    for (; st < ns; ++st) run_stage(tsrc, pre ? st + 2 - ns : ns - 1);
+    if (!pre) wait_vm_lds_and_barrier<0>();  // no DMA in flight
+    acc_fence_out(acc);  // every MFMA has written its accumulator before the epilogue reads it
+
+    // Column statistics; the waves of the upper 128 vocabulary rows hand theirs to those of the
+    // lower 128 through the W slot that the last stage left, which is loaded again only in step a
+    // of the next tile's first stage.
+    Partial* red = reinterpret_cast<Partial*>(smem + w2);  // [BN]
+    float* red2 = reinterpret_cast<float*>(red + BN);
+    const bool full = vt * BM + BM <= vocab;
+    const int vbase = vt * BM + wm * kWaveM + q4;
+    Partial own[TN];
+    float own2[TN];
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn) {
+      own2[tn] = kNegBig;
+      own[tn] = column_stats16<TM, TN, kTop2>(acc, tn, vbase, vocab, full, &own2[tn]);
+      if (wm == 1 && lane < 16) {
+        red[wn * kWaveN + tn * 16 + rho] = own[tn];
+        if (kTop2) red2[wn * kWaveN + tn * 16 + rho] = own2[tn];
+      }
+    }
+    __syncthreads();
+    if (wm == 0 && lane < 16) {
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn) {
+        const int c = wn * kWaveN + tn * 16 + rho;
+        const Partial o = red[c];
+        float m2 = kNegBig;
+        if (kTop2) m2 = top2_merge(own[tn].m, own2[tn], o.m, red2[c]);
+        const Partial p = partial_merge(own[tn], o);
+        const int row = rt * BN + c;
+        if (row < n_rows) {
+          part[static_cast<size_t>(row) * n_vtiles + vt] = p;
+          if (kTop2) part2[static_cast<size_t>(row) * n_vtiles + vt] = m2;
+        }
+      }
+    }
+    if (!next) break;
+    s = nxt;
+    vt = nvt;
+    rt = nrt;
+    src = nsrc;
+    __syncthreads();  // every wave is done with the reduction's slot (and, without pre, the ring)
+    if (!pre) start();
+  }
+}
+
+template <int TN, bool kTop2>
 __global__ __launch_bounds__(256, 1) void lmhead_tile_kernel(
     const uint16_t* __restrict__ h, const uint16_t* __restrict__ w, int n_rows, int hidden,
     int vocab, int n_vtiles, int n_rtiles, Partial* __restrict__ part,
     float* __restrict__ part2) {
-  constexpr int BN = kTileBN, BK = kTileBK;
-  constexpr int WM = 2, WN = 2, kWaves = WM * WN;
-  constexpr int kWaveM = BM / WM, kWaveN = BN / WN;
-  constexpr int TM = kWaveM / 16, TN = kWaveN / 16;
-  constexpr int kRowB = BK * 2;                   // 64 bytes per LDS row
-  constexpr int kStageBytes = (BM + BN) * kRowB;  // 32 KB
-  constexpr int kInst = (BM + BN) / 16;           // 1 KB wave instructions per stage
-  constexpr int kInstPerWave = kInst / kWaves;    // 8
-  constexpr int kRedBytes = WM * BN * (sizeof(Partial) + 4);
-  constexpr int kReads = TM + TN, kMfmas = TM * TN;
-  static_assert(RING == 4, "ring of 4 stages (steps go in pairs, and RING - 1 stages in flight)");
-  static_assert(BK == 32, "one 16x16x32 k step per stage");
-  static_assert(kInst % kWaves == 0, "stage loads split evenly over the waves");
-  static_assert(6 * kInstPerWave <= kMfmas && kReads == 2 * kInstPerWave, "interleave pattern");
-  static_assert(RING * kStageBytes + kRedBytes <= 160 * 1024, "ring and reduction fit in LDS");
-  static_assert((RING - 1) * kInstPerWave < 64, "vmcnt range");
-  __shared__ __attribute__((aligned(16))) uint8_t smem[RING * kStageBytes + kRedBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t smem[TileShape<TN>::kLdsBytes];
 
   // this workgroup's tiles: s0, s0 + step, ... below s_end
   const int n_tiles = n_vtiles * n_rtiles;
@@ -593,213 +786,33 @@ __global__ __launch_bounds__(256, 1) void lmhead_tile_kernel(
   }
   if (s0 >= s_end) return;  // whole workgroup
 
-  const int tid = threadIdx.x, lane = tid & 63;
   // the wave index is the same on every lane: taken as a scalar, so the LDS destinations of the
   // loads (M0) are scalar arithmetic
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave % WM, wn = wave / WM;
-  const int q4 = lane >> 4, l16 = lane & 15;
-  const int nk = hidden / BK;     // even (hidden is a multiple of 64), >= 2
-  const bool chain = nk >= RING;  // the tail of a tile issues the next tile's first stages
-
-  // Load instruction i of this wave covers tile rows 16 q .. 16 q + 15, q = wave * 8 + i (rows
-  // below BM are W, the rest h, so a wave loads from one operand only); lane L fetches row
-  // 16 q + L / 4, global chunk (L % 4) ^ swizzle(row) into LDS slot L % 4 of the row.  Rows past
-  // the end are clamped.  The loads are buffer loads into LDS: a resource per tile (its first
-  // row of the operand) in scalar registers, a byte offset per load instruction in a vector
-  // register, and the stage's column offset as the scalar offset.  (Global loads into LDS would
-  // count on the LDS-read counter as well, and the compiler then waits for every outstanding
-  // fragment read before each use of one.)
-  static_assert((BM / 16) % kInstPerWave == 0, "a wave loads from one operand");
-  const bool w_wave = wave * kInstPerWave * 16 < BM;
-  struct Src {
-    __amdgpu_buffer_rsrc_t rs;
-    uint32_t off[kInstPerWave];
-  };
-  auto set_src = [&](Src& d, int vt_, int rt_) {
-    const uint16_t* base =
-        w_wave ? w + static_cast<size_t>(vt_) * BM * hidden
-               : h + static_cast<size_t>(rt_) * BN * hidden;
-    const int last = w_wave ? vocab - 1 - vt_ * BM : n_rows - 1 - rt_ * BN;  // >= 0
-    d.rs = make_rsrc(base);
-#pragma unroll
-    for (int i = 0; i < kInstPerWave; ++i) {
-      const int q = wave * kInstPerWave + i;
-      const int row = 16 * q + (lane >> 2);
-      const int chunk = (lane & 3) ^ ((row >> 2) & 3);
-      const int r = min(w_wave ? row : row - BM, last);
-      d.off[i] = static_cast<uint32_t>(r * hidden * 2 + chunk * 16);
-    }
-  };
-  // A source chosen by value, field by field (a conditional reference to one of two sources
-  // makes the compiler take their addresses and keep them in scratch memory).
-  auto pick = [&](bool c, const Src& x, const Src& y) {
-    Src r;
-    r.rs = c ? x.rs : y.rs;
-#pragma unroll
-    for (int i = 0; i < kInstPerWave; ++i) r.off[i] = c ? x.off[i] : y.off[i];
-    return r;
-  };
-  // Stage `stage` of the tile described by d, into ring slot `slot`.
-  auto issue = [&](const Src& d, int stage, int slot) {
-    uint8_t* base = smem + slot * kStageBytes;
-#pragma unroll
-    for (int i = 0; i < kInstPerWave; ++i)
-      buffer_load_to_lds(d.rs, base + (wave * kInstPerWave + i) * 1024, d.off[i], stage * BK * 2);
-  };
-  // Fragment f of a stage (f < TM: W block f of this wave, else h block f - TM): lane l reads
-  // row rho(l % 16) = 4 (l % 4) + (l % 16) / 4 of the 16-row block, 16-byte chunk l / 16
-  // (k = 8 (l / 16) .. + 7).  Rows in their natural order (lane l, row l % 16) make every read a
-  // 2-way LDS bank conflict (rocprofv3 SQ_LDS_BANK_CONFLICT: 4 extra cycles per read, none with
-  // rho).  The MFMA then sees the block's rows permuted by rho, on both operands: accumulator
-  // register r of lane l holds vocabulary row 16 tm + rho(4 (l / 16) + r) = 16 tm + 4 r + l / 16
-  // of the wave's W rows, for position tn * 16 + rho(l % 16) of its h rows.
-  const int rho = 4 * (l16 & 3) + (l16 >> 2);
-  auto frag = [&](const uint8_t* st, int f) {
-    const int r = f < TM ? wm * kWaveM + f * 16 + rho : BM + wn * kWaveN + (f - TM) * 16 + rho;
-    return *reinterpret_cast<const bf16x8*>(st + r * kRowB + 16 * (q4 ^ ((r >> 2) & 3)));
-  };
-  auto read = [&](int slot, bf16x8 (&a)[TM], bf16x8 (&b)[TN]) {
-    const uint8_t* st = smem + slot * kStageBytes;
-#pragma unroll
-    for (int f = 0; f < TM; ++f) a[f] = frag(st, f);
-#pragma unroll
-    for (int f = 0; f < TN; ++f) b[f] = frag(st, TM + f);
-  };
-
-  f32x4 acc[TM][TN];
-  Partial* red = reinterpret_cast<Partial*>(smem + RING * kStageBytes);  // [WM][BN]
-  float* red2 = reinterpret_cast<float*>(red + WM * BN);
-
-  int s = s0, vt, rt;
-  band_tile(s, n_vtiles, n_rtiles, vt, rt);
-  Src src, nsrc;
-  set_src(src, vt, rt);
-  int slot0 = 0;  // ring slot of the current tile's stage 0
-#pragma unroll
-  for (int j = 0; j < RING; ++j) issue(src, min(j, nk - 1), j);
-  bf16x8 xa[TM], xb[TN], ya[TM], yb[TN];
-  wait_vm_lds_and_barrier<(RING - 1) * kInstPerWave>();  // stage 0 has landed
-  read(0, xa, xb);
-  for (;;) {
-    const int ns = s + step;
-    const bool next = ns < s_end;
-    int nvt = 0, nrt = 0;
-    if (next) {
-      band_tile(ns, n_vtiles, n_rtiles, nvt, nrt);
-      set_src(nsrc, nvt, nrt);
-    }
-    const bool pre = next && chain;
-    auto slot = [&](int kt) { return static_cast<int>(static_cast<unsigned>(slot0 + kt) % RING); };
-
-    // Step kt: the barrier, stage `stage` of p into the slot of stage kt, the fragments of
-    // stage kt + 1 into (na, nb) and the MFMAs of stage kt from (ca, cb).  Every step issues
-    // exactly one stage, so RING - 2 younger stages are in flight at each barrier.
-    auto body = [&](int kt, const Src& p, int stage, const bf16x8 (&ca)[TM],
-                    const bf16x8 (&cb)[TN], bf16x8 (&na)[TM], bf16x8 (&nb)[TN]) {
-      wait_vm_lds_and_barrier<(RING - 2) * kInstPerWave>();
-      uint8_t* lbase = smem + slot(kt) * kStageBytes;
-      const uint8_t* rbase = smem + slot(kt + 1) * kStageBytes;
-#pragma unroll
-      for (int i = 0; i < kMfmas; ++i) {
-        mfma16_tied(acc[i / TN][i % TN], ca[i / TN], cb[i % TN]);
-        if (i < 6 * kInstPerWave) {
-          const int grp = i / 6, r = i % 6;
-          if (r == 1)
-            buffer_load_to_lds(p.rs, lbase + (wave * kInstPerWave + grp) * 1024, p.off[grp],
-                               stage * BK * 2);
-          if (r == 3 || r == 5) {
-            const int f = 2 * grp + (r == 5);
-            if (f < TM)
-              na[f] = frag(rbase, f);
-            else
-              nb[f - TM] = frag(rbase, f);
-          }
-        }
-      }
-    };
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-      for (int b = 0; b < TN; ++b) acc[a][b] = f32x4{};
-    acc_fence_in(acc);  // the zeros are in place before the first MFMA reads them
-    // Steps go in pairs, alternating the two register sets (nk and RING are even, so a pair
-    // never straddles the end of this tile's stages).  Once this tile has no stage kt + RING,
-    // a step issues the next tile's first stages (or, without a next tile or with fewer than
-    // RING stages per tile, this tile's last stage again into the slot just freed, never read).
-    const Src tsrc = pick(pre, nsrc, src);
-    int kt = 0;
-    for (; kt + RING < nk; kt += 2) {
-      body(kt, src, kt + RING, xa, xb, ya, yb);
-      body(kt + 1, src, kt + 1 + RING, ya, yb, xa, xb);
-    }
-    for (; kt < nk; kt += 2) {
-      body(kt, tsrc, pre ? kt + RING - nk : nk - 1, xa, xb, ya, yb);
-      body(kt + 1, tsrc, pre ? kt + 1 + RING - nk : nk - 1, ya, yb, xa, xb);
-    }
-    if (!pre) wait_vm_lds_and_barrier<0>();  // no DMA in flight
-    acc_fence_out(acc);  // every MFMA has written its accumulator before the epilogue reads it
-
-    const bool full = vt * BM + BM <= vocab;
-    const int vbase = vt * BM + wm * kWaveM + q4;
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn) {
-      float m2 = kNegBig;
-      const Partial p = column_stats16<TM, TN, kTop2>(acc, tn, vbase, vocab, full, &m2);
-      if (lane < 16) {
-        red[wm * BN + wn * kWaveN + tn * 16 + rho] = p;
-        if (kTop2) red2[wm * BN + wn * kWaveN + tn * 16 + rho] = m2;
-      }
-    }
-    __syncthreads();
-    for (int c = tid; c < BN; c += kWaves * 64) {
-      Partial p = red[c];
-      float m2 = kTop2 ? red2[c] : kNegBig;
-#pragma unroll
-      for (int q = 1; q < WM; ++q) {
-        const Partial o = red[q * BN + c];
-        if (kTop2) m2 = top2_merge(p.m, m2, o.m, red2[q * BN + c]);
-        p = partial_merge(p, o);
-      }
-      const int row = rt * BN + c;
-      if (row < n_rows) {
-        part[static_cast<size_t>(row) * n_vtiles + vt] = p;
-        if (kTop2) part2[static_cast<size_t>(row) * n_vtiles + vt] = m2;
-      }
-    }
-    if (!next) break;
-    s = ns;
-    vt = nvt;
-    rt = nrt;
-    src = nsrc;
-    if (pre) {
-      slot0 = (slot0 + nk) % RING;  // stage 0 of this tile is in xa, xb already
-    } else {
-      slot0 = 0;
-      __syncthreads();  // every wave is done with the ring
-#pragma unroll
-      for (int j = 0; j < RING; ++j) issue(src, min(j, nk - 1), j);
-      wait_vm_lds_and_barrier<(RING - 1) * kInstPerWave>();
-      read(0, xa, xb);
-    }
-  }
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave < 2)
+    tile_run<TN, kTop2, true>(smem, h, w, n_rows, hidden, vocab, n_vtiles, n_rtiles, part, part2,
+                              s0, step, s_end, wave);
+  else
+    tile_run<TN, kTop2, false>(smem, h, w, n_rows, hidden, vocab, n_vtiles, n_rtiles, part, part2,
+                               s0, step, s_end, wave);
 }
 
-// Tile kernel of the large-batch path: 256 x 256 tiles, 4 waves of 128 x 128, ring of 4
-// (128 KB LDS, one workgroup per compute unit).
+// Tile kernel of the large-batch path: 4 waves, one workgroup per compute unit.  Measured with
+// 1024 positions of a 126464 x 4096 head: 807 us, against 945 us with stages of 32 columns (64
+// contiguous bytes per row and load: twice the L2 requests); 4096 positions: 3.03 against 3.46 ms.
 // Measured and dropped (with 32x32x16 blocks): 8 waves of 128 x 64 (10.55 ms), 256 x 128 tiles
 // with a ring of 3 at two workgroups per compute unit (11.8 ms), stages reaching LDS through
-// registers (9.65 ms), 64-column stages with one barrier per 64 MFMAs (10.1 ms), 384 x 256 tiles
-// (384 accumulators per lane: the compiler spills).
+// registers (9.65 ms), 384 x 256 tiles (384 accumulators per lane: the compiler spills).
 template <bool kTop2>
 hipError_t launch_tile(int n_rows, int hidden, int vocab, const void* h, const void* w,
                        Partial* part, float* part2, hipStream_t s) {
+  constexpr int kTn = 8;
   const int n_vtiles = tile_vtiles(vocab);
-  const int n_rtiles = (n_rows + kTileBN - 1) / kTileBN;
+  const int n_rtiles = (n_rows + 32 * kTn - 1) / (32 * kTn);
   const int n_tiles = n_vtiles * n_rtiles;
   const int groups = n_tiles >= kTileGroups ? kTileGroups : n_tiles;
-  hipLaunchKernelGGL((lmhead_tile_kernel<kTileBM, kTileRing, kTop2>), dim3(groups), dim3(256), 0,
-                     s, static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(w), n_rows,
+  hipLaunchKernelGGL((lmhead_tile_kernel<kTn, kTop2>), dim3(groups), dim3(256), 0, s,
+                     static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(w), n_rows,
                      hidden, vocab, n_vtiles, n_rtiles, part, part2);
   return hipGetLastError();
 }
