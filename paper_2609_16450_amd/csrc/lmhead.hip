@@ -8,6 +8,8 @@
 // Orientation: the MFMA "row" dimension is the vocabulary and the "column" dimension is the
 // block position, so every lane owns one position and reduces the logits it holds in
 // registers before a single cross-half exchange.
+#include <type_traits>
+
 #include "attn_small.hpp"
 #include "eb_common.hpp"
 #include "eb_internal.hpp"
@@ -23,7 +25,10 @@ namespace {
 // above 768 rows) streams its share of the slice from HBM straight into MFMA A-operand
 // registers, keeping kDepth k-steps of loads in flight; h, the B operand shared by all waves,
 // goes through a double-buffered LDS chunk.  Every W byte is read once, by one lane, with no
-// LDS round trip.  (Loading h per wave straight into registers instead, with no LDS and no
+// LDS round trip, in whole cache lines (line_to_frag).  Bound by HBM: 32 positions of a 126464 x
+// 4096 head take 173 us (6.0 TB/s) with whole lines against 177.5 us with half lines on one
+// machine, 64 positions 177.6 against 185 us; of a 152064 x 3584 head 185.5 against 200 us and
+// 197.6 against 214 us.  (Loading h per wave straight into registers instead, with no LDS and no
 // barrier, measured 237 us against 203 us at 32 positions: the per-wave h traffic from L2 costs
 // more than the shared chunks.)
 // ---------------------------------------------------------------------------------------
@@ -32,10 +37,26 @@ namespace {
 #endif
 constexpr int kStreamGroups = EB_STREAM_GROUPS;  // workgroups (256: one per compute unit)
 
-// The streaming kernel uses 16x16x32 MFMA tiles (mfma16).  A lane of the A operand holds 8
-// consecutive k-values of row l % 16 and the four lanes of a row cover 64 contiguous bytes, so
-// each load instruction reads 16 rows x 64 B of W (a 32x32x16 layout reads half that run per row
-// and measured 4.65 TB/s at best against 5.4).
+// The streaming kernel uses 16x16x32 MFMA tiles (mfma16; 32x32x16 tiles measured 4.65 TB/s at best
+// against 5.4).  A lane of the A operand holds 8 k-values of row l % 16, so loads straight into
+// that layout would read 16 rows x 64 bytes, half a cache line per row.  Instead a k-step is 64
+// columns of a 16-row tile in two loads of 8 rows x 128 bytes: lane l loads 16-byte chunk l / 8 of
+// row l % 8 (v0) and of row 8 + l % 8 (v1).  line_to_frag exchanges v0 and v1 between lanes l and
+// l ^ 8, after which lane l holds row l % 16 in both, chunk 2 (l / 16) in the first and
+// 2 (l / 16) + 1 in the second: the A operands of two MFMAs whose contraction indices are the even
+// and the odd chunks of the step.  h is read from LDS in the same order.
+__device__ __forceinline__ void line_to_frag(const u32x4& v0, const u32x4& v1, bf16x8& even,
+                                             bf16x8& odd) {
+  constexpr int kRor8 = 0x128;  // DPP row_ror:8: from the lane 8 away in the row of 16
+  u32x4 e, o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    e[i] = __builtin_amdgcn_update_dpp(v0[i], v1[i], kRor8, 0xf, 0xc, false);  // lanes 8..15
+    o[i] = __builtin_amdgcn_update_dpp(v1[i], v0[i], kRor8, 0xf, 0x3, false);  // lanes 0..7
+  }
+  even = __builtin_bit_cast(bf16x8, e);
+  odd = __builtin_bit_cast(bf16x8, o);
+}
 
 // Second-largest logit (with multiplicity) of the union of two sets whose largest values are
 // m_a, m_b and second-largest m2_a, m2_b.  Exact and order-free, so every merge order gives
@@ -50,10 +71,10 @@ __device__ __forceinline__ float top2_shfl_merge(float m, float m2, int mask) {
 }
 
 // kTop2: also track the second-largest logit of each (row, slice) into part2.
-// kWaves waves per workgroup, TM 16-row tiles per wave, NT 16-position tiles.
+// kWaves waves per workgroup, NL 8-row loads (half MFMA tiles) per wave, NT 16-position tiles.
 // kAttnD != 0: workgroups n_slices and up run the small block attention (head dimension kAttnD)
 // on unit blockIdx.x - n_slices of ap; the dispatcher starts them as the slices finish.
-template <int kWaves, int TM, int NT, int kDepth, bool kTop2, int kAttnD>
+template <int kWaves, int NL, int NT, int kDepth, bool kTop2, int kAttnD>
 __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
     const uint16_t* __restrict__ h, const uint16_t* __restrict__ w, int n_rows, int hidden,
     int vocab, int rows_per_wg, Partial* __restrict__ part, float* __restrict__ part2,
@@ -65,9 +86,10 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
       return;
     }
   }
+  constexpr int TM = (NL + 1) / 2;     // 16-row tiles; the last one may lack its upper rows
   constexpr int KC = 1024 / NT;        // h columns per LDS chunk
   constexpr int kPitch = KC + 8;       // LDS row pitch (bf16)
-  constexpr int kSpc = KC / 32;        // k-steps per chunk
+  constexpr int kSpc = KC / 64;        // k-steps per chunk
   constexpr int kHRows = NT * 16;
   constexpr int kHChunks16 = kHRows * KC / 8;
   constexpr int kThreads = kWaves * 64;
@@ -85,23 +107,23 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
   const int wb = vb + wave * rw;
   const int we = min(ve, wb + rw);
 
-  // Unconditional loads with clamped addresses, as in the 32x32 kernel.
+  // Unconditional loads with clamped addresses: rows 8 i + l % 8 of the wave's share.
   const int wlast = max(min(we, vocab) - 1, 0);
-  const uint16_t* wp[TM];
+  const uint16_t* wp[NL];
 #pragma unroll
-  for (int tm = 0; tm < TM; ++tm) {
-    const int row = min(wb + tm * 16 + l16, wlast);
-    wp[tm] = w + static_cast<size_t>(row) * hidden + 8 * grp;
+  for (int i = 0; i < NL; ++i) {
+    const int row = min(wb + i * 8 + (lane & 7), wlast);
+    wp[i] = w + static_cast<size_t>(row) * hidden + 8 * (lane >> 3);
   }
-  const int nsteps = hidden / 32;
+  const int nsteps = hidden / 64;
   const int nsteps_p = (nsteps + kDepth - 1) / kDepth * kDepth;
   const int nchunks = (hidden + KC - 1) / KC;
 
-  u32x4 buf[kDepth][TM];
+  u32x4 buf[kDepth][NL];
   auto issue = [&](int j, int step) {
     const int st = min(step, nsteps - 1);
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm) buf[j][tm] = *reinterpret_cast<const u32x4*>(wp[tm] + 32 * st);
+    for (int i = 0; i < NL; ++i) buf[j][i] = *reinterpret_cast<const u32x4*>(wp[i] + 64 * st);
   };
   u32x4 hreg[kHPer];
   auto load_h = [&](int c) {
@@ -137,17 +159,19 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
   if (nchunks > 1) load_h(1);
 
   auto consume = [&](int g, int j) {
-    const uint16_t* hb = hs[(g / kSpc) & 1] + (g % kSpc) * 32 + 8 * grp + 32 * j;
-    bf16x8 b[NT];
+    const uint16_t* hb = hs[(g / kSpc) & 1] + (g % kSpc) * 64 + 16 * grp + 64 * j;
+    bf16x8 a[TM][2];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-      b[nt] = *reinterpret_cast<const bf16x8*>(hb + (nt * 16 + l16) * kPitch);
+    for (int tm = 0; tm < TM; ++tm)  // (upper rows that are not there repeat the lower ones)
+      line_to_frag(buf[j][2 * tm], buf[j][min(2 * tm + 1, NL - 1)], a[tm][0], a[tm][1]);
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm) {
-      const bf16x8 a = __builtin_bit_cast(bf16x8, buf[j][tm]);
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[tm][nt] = mfma16(a, b[nt], acc[tm][nt]);
-    }
+      for (int nt = 0; nt < NT; ++nt) {
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(hb + (nt * 16 + l16) * kPitch + 8 * i);
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) acc[tm][nt] = mfma16(a[tm][i], b, acc[tm][nt]);
+      }
   };
   auto chunk_boundary = [&](int g) {
     if (g > 0 && g % kSpc == 0) {
@@ -231,9 +255,10 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
 // k-steps of W loads in flight per wave with 16 waves (measured on MI355X; the macro exists so
 // that other settings can be built and timed).
 #ifndef EB_STREAM_DEPTH
-#define EB_STREAM_DEPTH 8
+#define EB_STREAM_DEPTH 4
 #endif
 constexpr int kStreamShape = 16;  // rows (and positions) per MFMA tile
+constexpr int kStreamLoad = 8;    // rows per load
 constexpr int kStreamDepth = EB_STREAM_DEPTH;
 // 16 waves per workgroup while each wave's share of the slice fits in kStreamMaxTm16 row tiles
 // (at 1024 threads a lane has 128 VGPRs; four tiles with two or more position tiles spill), else
@@ -244,17 +269,18 @@ constexpr int kStreamMaxTm8 = 8;
 
 struct StreamPlan {
   int groups, rows_per_wg, waves, tm;  // tm: MFMA row tiles per wave
+  int nl;                              // 8-row loads per wave
 };
 
 StreamPlan stream_plan(int vocab) {
   const int groups = min(kStreamGroups, (vocab + 31) / 32);
   const int rows = (vocab + groups - 1) / groups;
-  auto tiles = [&](int waves) {
+  auto plan = [&](int waves) {
     const int rw = (rows + waves - 1) / waves;
-    return (rw + kStreamShape - 1) / kStreamShape;
+    return StreamPlan{groups, rows, waves, (rw + kStreamShape - 1) / kStreamShape,
+                      (rw + kStreamLoad - 1) / kStreamLoad};
   };
-  if (tiles(16) <= kStreamMaxTm16) return StreamPlan{groups, rows, 16, tiles(16)};
-  return StreamPlan{groups, rows, 8, tiles(8)};
+  return plan(16).tm <= kStreamMaxTm16 ? plan(16) : plan(8);
 }
 
 constexpr int kStreamMaxRows = 64;  // n_rows handled by the streaming kernel
@@ -273,40 +299,39 @@ struct HostedAttn {
   int units, attn_d;
 };
 
-template <int kWaves, int TM, int NT, bool kTop2, int kAttnD = 0>
-hipError_t launch_stream_tm(int n_rows, int hidden, int vocab, const StreamPlan& pl,
+template <int kWaves, int NL, int NT, bool kTop2, int kAttnD = 0>
+hipError_t launch_stream_nl(int n_rows, int hidden, int vocab, const StreamPlan& pl,
                             const void* h, const void* w, Partial* part, float* part2,
                             hipStream_t s, const HostedAttn& ha) {
   // 16 waves: up to 16 W registers in flight per lane (16 bytes each; 8 with four position
-  // tiles), at most kStreamDepth k-steps.  8 waves: two k-steps (more measured no faster).
-  constexpr int kBudget = kWaves == 8 ? 2 * TM : (NT >= 4 ? 8 : 16);
-  constexpr int D0 = kBudget / TM >= 1 ? kBudget / TM : 1;
-  constexpr int D = (kWaves == 16 && D0 > kStreamDepth) ? kStreamDepth : D0;
-  // a power of two that divides the per-chunk step count
-  constexpr int Dp = D >= 8 ? 8 : (D >= 4 ? 4 : (D >= 2 ? 2 : 1));
+  // tiles, where more spill and 4 measured 182 against 177 us), at most kStreamDepth k-steps, a
+  // power of two that divides the per-chunk step count.  8 waves: one k-step (more measured no
+  // faster).
+  constexpr int D = kWaves == 8 ? 1 : (NT >= 4 ? 8 : 16) / NL;
+  constexpr int Dp = D >= kStreamDepth ? kStreamDepth : (D >= 4 ? 4 : (D >= 2 ? 2 : 1));
   const int extra = kAttnD != 0 ? ha.units : 0;
-  hipLaunchKernelGGL((lmhead_stream16_kernel<kWaves, TM, NT, Dp, kTop2, kAttnD>),
+  hipLaunchKernelGGL((lmhead_stream16_kernel<kWaves, NL, NT, Dp, kTop2, kAttnD>),
                      dim3(pl.groups + extra), dim3(kWaves * 64), 0, s,
                      static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(w), n_rows,
                      hidden, vocab, pl.rows_per_wg, part, part2, pl.groups, ha.p);
   return hipGetLastError();
 }
 
-// 16 waves, TM row tiles: the variant for the hosted attention's head dimension.
-template <int TM, int NT, bool kTop2>
+// 16 waves, NL 8-row loads: the variant for the hosted attention's head dimension.
+template <int NL, int NT, bool kTop2>
 hipError_t launch_stream16(int n_rows, int hidden, int vocab, const StreamPlan& pl,
                            const void* h, const void* w, Partial* part, float* part2,
                            hipStream_t s, const HostedAttn& ha) {
   if constexpr (!kTop2) {
     if (ha.attn_d == 128)
-      return launch_stream_tm<16, TM, NT, false, 128>(n_rows, hidden, vocab, pl, h, w, part,
+      return launch_stream_nl<16, NL, NT, false, 128>(n_rows, hidden, vocab, pl, h, w, part,
                                                       part2, s, ha);
     if (ha.attn_d == 64)
-      return launch_stream_tm<16, TM, NT, false, 64>(n_rows, hidden, vocab, pl, h, w, part,
+      return launch_stream_nl<16, NL, NT, false, 64>(n_rows, hidden, vocab, pl, h, w, part,
                                                      part2, s, ha);
   }
   if (ha.attn_d != 0) return hipErrorInvalidValue;  // excluded by lmhead_hosts_attn
-  return launch_stream_tm<16, TM, NT, kTop2>(n_rows, hidden, vocab, pl, h, w, part, part2, s,
+  return launch_stream_nl<16, NL, NT, kTop2>(n_rows, hidden, vocab, pl, h, w, part, part2, s,
                                              ha);
 }
 
@@ -315,32 +340,32 @@ template <int NT, bool kTop2>
 hipError_t launch_stream(int n_rows, int hidden, int vocab, const void* h, const void* w,
                          Partial* part, float* part2, hipStream_t s, const HostedAttn& ha) {
   const StreamPlan pl = stream_plan(vocab);
+  auto go16 = [&](auto nl) {
+    return launch_stream16<nl.value, NT, kTop2>(n_rows, hidden, vocab, pl, h, w, part, part2, s,
+                                                ha);
+  };
   if (pl.waves == 16) {
-    switch (pl.tm) {
-      case 1:
-        return launch_stream16<1, NT, kTop2>(n_rows, hidden, vocab, pl, h, w, part, part2, s, ha);
-      case 2:
-        return launch_stream16<2, NT, kTop2>(n_rows, hidden, vocab, pl, h, w, part, part2, s, ha);
-      case 3:
-        return launch_stream16<3, NT, kTop2>(n_rows, hidden, vocab, pl, h, w, part, part2, s, ha);
+    switch (pl.nl) {
+      case 1: return go16(std::integral_constant<int, 1>{});
+      case 2: return go16(std::integral_constant<int, 2>{});
+      case 3: return go16(std::integral_constant<int, 3>{});
+      case 4: return go16(std::integral_constant<int, 4>{});
+      case 5: return go16(std::integral_constant<int, 5>{});
+      case 6: return go16(std::integral_constant<int, 6>{});
       default: return hipErrorInvalidValue;  // excluded by stream_plan
     }
   }
   if (ha.attn_d != 0) return hipErrorInvalidValue;  // excluded by lmhead_hosts_attn
   // More than 48 tiles of rows per workgroup: the 8-wave shape has 7 or 8 tiles per wave.
-  switch (pl.tm) {
-    case 7:
-      if constexpr (NT < 4)
-        return launch_stream_tm<8, 7, NT, kTop2>(n_rows, hidden, vocab, pl, h, w, part, part2, s,
-                                                 ha);
-      return hipErrorInvalidValue;
-    case 8:
-      if constexpr (NT < 4)
-        return launch_stream_tm<8, 8, NT, kTop2>(n_rows, hidden, vocab, pl, h, w, part, part2, s,
-                                                 ha);
-      return hipErrorInvalidValue;
-    default: return hipErrorInvalidValue;  // excluded by use_stream
+  if constexpr (NT < 4) {
+    if (pl.tm == 7)
+      return launch_stream_nl<8, 14, NT, kTop2>(n_rows, hidden, vocab, pl, h, w, part, part2, s,
+                                                ha);
+    if (pl.tm == 8)
+      return launch_stream_nl<8, 16, NT, kTop2>(n_rows, hidden, vocab, pl, h, w, part, part2, s,
+                                                ha);
   }
+  return hipErrorInvalidValue;  // excluded by use_stream
 }
 
 template <bool kTop2>

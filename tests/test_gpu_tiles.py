@@ -1,4 +1,4 @@
-"""LM-head tile kernel (more than 64 positions) at the edges of its tiles, against the oracle."""
+"""LM-head kernels at the edges of their tiles, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -38,5 +38,34 @@ def test_tile_edges(rows, hidden):
     # An fp32 sum of d products of size |w||h| <= 20 is off by at most d 2^-24 20 < 4e-4 (d = 320),
     # which is also the relative error of a probability; 1e-3 as in the other parity tests.
     np.testing.assert_array_equal(arg.cpu().numpy(), ref["argmax"])
+    for got, want in ((conf, "conf"), (ent, "entropy"), (top, "max_logit"), (gap, "top2_gap")):
+        np.testing.assert_allclose(got.cpu().numpy(), ref[want], rtol=0, atol=1e-3, err_msg=want)
+
+
+@pytest.mark.parametrize("hidden", [64, 192, 1088])
+@pytest.mark.parametrize("rows", [1, 16, 17, 33, 64])
+@pytest.mark.parametrize("vocab", [1, 40, 30000, 40000, 70000, 100001, 152064, 190000])
+def test_stream_loads(rows, hidden, vocab):
+    """LM-head streaming kernel: one to six 8-row loads per wave (with whole and half 16-row tiles
+    and waves without rows), one, two and four position tiles, hidden sizes of one k-step, of less
+    than a chunk and of a chunk and a remainder."""
+    print(f"stream rows={rows} hidden={hidden} vocab={vocab}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(rows + 100 * hidden + vocab)
+    w = torch.randn(vocab, hidden, generator=g, device="cuda").mul_(hidden ** -0.5).bfloat16()
+    h = torch.randn(rows, hidden, generator=g, device="cuda")
+    t = torch.randint(0, vocab, (rows,), generator=g, device="cuda")
+    t[-1] = vocab - 1
+    u = w[t].float()
+    h = (h + 12.0 * u / u.norm(dim=1, keepdim=True)).bfloat16()
+    conf, ent, gap, top = (torch.empty(rows, device="cuda") for _ in range(4))
+    arg = torch.empty(rows, dtype=torch.int32, device="cuda")
+    eb_lmhead_features(h, w, conf, ent, arg, gap, max_logit=top)
+    z = h.double() @ w.double().t()
+    ref = oracle.eb_oracle.confidence_stats(z.cpu().numpy())
+    # fp32 sums of d products, |w||h| <= 50: d 2^-24 50 < 4e-3 at worst (d = 1088) and some
+    # sqrt(d) of that, 1e-4, for sums of random signs
+    two = torch.topk(z, min(2, vocab), dim=1).values
+    clear = ((two[:, 0] - two[:, -1] > 1e-3) | (vocab == 1)).cpu().numpy()
+    np.testing.assert_array_equal(arg.cpu().numpy()[clear], ref["argmax"][clear])
     for got, want in ((conf, "conf"), (ent, "entropy"), (top, "max_logit"), (gap, "top2_gap")):
         np.testing.assert_allclose(got.cpu().numpy(), ref[want], rtol=0, atol=1e-3, err_msg=want)
