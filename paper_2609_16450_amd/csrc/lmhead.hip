@@ -828,18 +828,55 @@ __global__ __launch_bounds__(256, 1) void lmhead_tile_kernel(
 // Measured and dropped (with 32x32x16 blocks): 8 waves of 128 x 64 (10.55 ms), 256 x 128 tiles
 // with a ring of 3 at two workgroups per compute unit (11.8 ms), stages reaching LDS through
 // registers (9.65 ms), 384 x 256 tiles (384 accumulators per lane: the compiler spills).
-template <bool kTop2>
-hipError_t launch_tile(int n_rows, int hidden, int vocab, const void* h, const void* w,
-                       Partial* part, float* part2, hipStream_t s) {
-  constexpr int kTn = 8;
+template <int TN, bool kTop2>
+hipError_t launch_tile_tn(int n_rows, int hidden, int vocab, const void* h, const void* w,
+                          Partial* part, float* part2, hipStream_t s) {
   const int n_vtiles = tile_vtiles(vocab);
-  const int n_rtiles = (n_rows + 32 * kTn - 1) / (32 * kTn);
+  const int n_rtiles = (n_rows + 32 * TN - 1) / (32 * TN);
   const int n_tiles = n_vtiles * n_rtiles;
   const int groups = n_tiles >= kTileGroups ? kTileGroups : n_tiles;
-  hipLaunchKernelGGL((lmhead_tile_kernel<kTn, kTop2>), dim3(groups), dim3(256), 0, s,
+  hipLaunchKernelGGL((lmhead_tile_kernel<TN, kTop2>), dim3(groups), dim3(256), 0, s,
                      static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(w), n_rows,
                      hidden, vocab, n_vtiles, n_rtiles, part, part2);
   return hipGetLastError();
+}
+
+// Width of the position tiles in 32 positions: the one whose rounds of kTileGroups tiles cost
+// least, a tile of 32 TN positions counting TN + 3.  Per round of tiles (126464 x 4096, 384 to
+// 512 positions) TN = 3 .. 8 take 59, 66, 77, 87, 98 and 107 us: MFMAs and h loads go with TN,
+// the rest (W's loads, LDS traffic and latency) counts as three.  Up to 160 positions the tiles
+// are bound by W from HBM and the narrowest that covers them is the best as well (128 positions:
+// 183 us at TN = 4, 209 us at TN = 8).  On equal cost the wider tile, which reads less from L2.
+// Results do not depend on the width: a column's statistics are formed per vocabulary tile.
+int tile_width(int n_rows, int vocab) {
+  const long n_vtiles = tile_vtiles(vocab);
+  int best = 0;
+  long best_cost = 0;
+  for (int tn = 8; tn >= 3; --tn) {
+    const long n_tiles = n_vtiles * ((n_rows + 32 * tn - 1) / (32 * tn));
+    const long cost = (n_tiles + kTileGroups - 1) / kTileGroups * (tn + 3);
+    if (best == 0 || cost < best_cost) {
+      best = tn;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+template <bool kTop2>
+hipError_t launch_tile(int n_rows, int hidden, int vocab, const void* h, const void* w,
+                       Partial* part, float* part2, hipStream_t s) {
+  auto go = [&](auto tn) {
+    return launch_tile_tn<tn.value, kTop2>(n_rows, hidden, vocab, h, w, part, part2, s);
+  };
+  switch (tile_width(n_rows, vocab)) {
+    case 3: return go(std::integral_constant<int, 3>{});
+    case 4: return go(std::integral_constant<int, 4>{});
+    case 5: return go(std::integral_constant<int, 5>{});
+    case 6: return go(std::integral_constant<int, 6>{});
+    case 7: return go(std::integral_constant<int, 7>{});
+    default: return go(std::integral_constant<int, 8>{});
+  }
 }
 
 // ---------------------------------------------------------------------------------------
