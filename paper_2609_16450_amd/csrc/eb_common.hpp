@@ -12,6 +12,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // at any float address
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -32,6 +33,12 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // accumulator register r of lane l is C[4 * (l / 16) + r][l % 16].
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// 16x16 output tile, K = 4 per instruction, fp32 throughout.  Lane l holds A[l % 16][l / 16] and
+// B[l / 16][l % 16]; accumulator register r of lane l is C[4 * (l / 16) + r][l % 16].
+__device__ __forceinline__ f32x4 mfma16_f32(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -102,7 +109,8 @@ struct alignas(16) Partial {
 __device__ __forceinline__ Partial partial_empty() { return Partial{kNegBig, 0.f, 0.f, kNoIndex}; }
 
 // Merge two partials.  The result does not depend on argument order for m and idx; s and t
-// are combined in the order given (callers fix that order for determinism).
+// are combined in the order given (callers fix that order for determinism), with the multiply-adds
+// written out so that every kernel that merges rounds alike.
 __device__ __forceinline__ Partial partial_merge(const Partial& a, const Partial& b) {
   const float M = fmaxf(a.m, b.m);
   // <= 0; clamped so that an empty side (s = 0, m = kNegBig) contributes 0 * finite = 0
@@ -112,8 +120,8 @@ __device__ __forceinline__ Partial partial_merge(const Partial& a, const Partial
   const float fb = fast_exp2(db);
   Partial r;
   r.m = M;
-  r.s = a.s * fa + b.s * fb;
-  r.t = fa * (a.t + a.s * da) + fb * (b.t + b.s * db);
+  r.s = fmaf(a.s, fa, b.s * fb);
+  r.t = fmaf(fa, fmaf(a.s, da, a.t), fb * fmaf(b.s, db, b.t));
   r.idx = (a.m > b.m) ? a.idx : (b.m > a.m) ? b.idx : min(a.idx, b.idx);
   return r;
 }
@@ -147,7 +155,7 @@ __device__ __forceinline__ Partial wave_finish(const Partial& acc) {
   const float d = fmaxf((acc.m - M) * kLog2e, -1.0e30f);  // empty lane: 2^d = 0
   const float f = fast_exp2(d);
   float s = acc.s * f;
-  float t = f * (acc.t + acc.s * d);
+  float t = f * fmaf(acc.s, d, acc.t);
   for (int mask = 32; mask >= 1; mask >>= 1) {
     s += __shfl_xor(s, mask);
     t += __shfl_xor(t, mask);
