@@ -1,0 +1,59 @@
+"""fp32 kernels at the edges of their tiles, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_16450_amd import Ragged, eb_block_attn_dual, eb_lmhead_features
+
+pytestmark = pytest.mark.gpu
+
+
+def _cu(lens):
+    return np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+
+
+# Query rows per K/V head at, below and above 16; keys below one 16-key chunk, one chunk per wave
+# (128), a few more, and empty segments and blocks.
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("group", [1, 3])
+@pytest.mark.parametrize("blocks,prefix,suffix", [
+    ([1], [0], [0]), ([16], [112], [0]), ([5, 0, 6], [3, 7, 300], [0, 1, 33]),
+    ([17, 33], [0, 95], [1, 0])])
+def test_attention_f32(blocks, prefix, suffix, group, head_dim):
+    print(f"attn f32 {blocks} {prefix} {suffix} G={group} D={head_dim}", flush=True)
+    rng = np.random.default_rng([head_dim, group, *blocks])
+    hkv, T, S, U = 2, sum(blocks), sum(prefix), sum(suffix)
+    def x(*s): return rng.standard_normal(s, dtype=np.float32)
+    q = x(T, hkv * group, head_dim)
+    kv = [x(n, hkv, head_dim) for n in (T, T, S, S, U, U)]
+    ref = oracle.block_attention(q, *kv[:4], _cu(blocks), _cu(prefix), hkv * group, hkv,
+                                 k_suf=kv[4], v_suf=kv[5], cu_suffix=_cu(suffix))
+    out = torch.full(q.shape, 7.0, device="cuda")
+    eb_block_attn_dual(Ragged.from_lengths(blocks, prefix), torch.from_numpy(_cu(suffix)).cuda(),
+                       max(suffix), torch.from_numpy(q).cuda(),
+                       *(torch.from_numpy(a).cuda() for a in kv), out)
+    # scores of size |q||k| / sqrt(d) < 16 off by some 128 2^-24 16 / sqrt(128): 1e-5 in a weight
+    np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
+
+
+# Slices of 64 and of 256 rows (70001 x 300 positions), odd and unaligned hidden sizes with and
+# without whole 64-column rounds, partial position tiles, waves without vocabulary rows.
+@pytest.mark.parametrize("rows,hidden,vocab", [
+    (1, 1, 1), (2, 3, 5), (31, 64, 65), (32, 16, 256), (33, 333, 300), (64, 100, 2049),
+    (300, 65, 70001)])
+def test_lmhead_f32(rows, hidden, vocab):
+    print(f"lmhead f32 rows={rows} hidden={hidden} vocab={vocab}", flush=True)
+    rng = np.random.default_rng([rows, hidden, vocab])
+    w = rng.standard_normal((vocab, hidden), dtype=np.float32) / np.float32(np.sqrt(hidden))
+    h = 2.0 * rng.standard_normal((rows, hidden), dtype=np.float32)
+    ref = oracle.lmhead_confidence(h, w)
+    conf, ent, gap, top = (torch.empty(rows, device="cuda") for _ in range(4))
+    arg = torch.empty(rows, dtype=torch.int32, device="cuda")
+    eb_lmhead_features(torch.from_numpy(h).cuda(), torch.from_numpy(w).cuda(), conf, ent, arg, gap,
+                       max_logit=top)
+    np.testing.assert_array_equal(arg.cpu().numpy(), ref["argmax"])
+    # d products of |w||h| < 40 in fp32: below d 2^-24 40 = 8e-4 (d = 333) at worst, some sqrt(d)
+    # of that for random signs
+    for got, want in ((conf, "conf"), (ent, "entropy"), (top, "max_logit"), (gap, "top2_gap")):
+        np.testing.assert_allclose(got.cpu().numpy(), ref[want], rtol=0, atol=5e-5, err_msg=want)
