@@ -94,7 +94,7 @@ __global__ __launch_bounds__(kFinishThreads) void step_finish_kernel(
     return;
   }
   unmask_block<kThreshold, kFinishThreads>(b, ap.cu_block, conf, argmax, tau,
-                                           RuleArgs{nullptr, 0.f, 0}, masked, tokens, unmask,
+                                           RuleArgs{nullptr, 0.f}, masked, tokens, unmask,
                                            n_commit, resolved);
 }
 

@@ -19,6 +19,136 @@ __global__ __launch_bounds__(kThreads) void unmask_kernel(
                   resolved);
 }
 
+// Budgeted block step (Eq. prelim-update with a budget m), one workgroup per block: a masked row
+// passes when conf >= tau_b or fewer than m masked rows of the block rank above it (larger conf, or
+// equal conf and a lower row); the fallback and the commit are those of unmask_block.
+//
+// Each row's rank is counted once, by four lanes that share the block's rows four at a time from
+// LDS (an unmasked row is a NaN there, which compares with nothing).  Bound by latency, as the
+// counts of a block of 256 rows are 65536 compares: 64 blocks of 16 to 256 rows take 9.1 us, where
+// one thread per row counting twice took 52 us.  Blocks of more than kRankTile rows are staged
+// tile by tile.
+constexpr int kTopmThreads = 1024;
+constexpr int kRankLanes = 4;                            // lanes that count one row's rank
+constexpr int kRankRows = kTopmThreads / kRankLanes;     // rows per round
+constexpr int kRankTile = 2048;                          // rows of a block staged at once
+
+__global__ __launch_bounds__(kTopmThreads) void unmask_topm_kernel(
+    const int32_t* __restrict__ cu_block, const float* __restrict__ conf,
+    const int32_t* __restrict__ argmax, const float* __restrict__ tau, int budget,
+    uint8_t* __restrict__ masked, int32_t* __restrict__ tokens, uint8_t* __restrict__ unmask,
+    int32_t* __restrict__ n_commit, uint8_t* __restrict__ resolved) {
+  constexpr int kWaves = kTopmThreads / 64;
+  __shared__ __attribute__((aligned(16))) float s_key[kRankTile];
+  __shared__ int s_masked[kWaves], s_pass[kWaves];
+  __shared__ Best s_best[kWaves];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int beg = cu_block[b], len = cu_block[b + 1] - beg;
+  const float tb = tau[b];
+  // rows t0 .. t0 + kRankTile - 1 of the block into LDS, NaN past the end
+  auto stage = [&](int t0) {
+    for (int j = tid; j < kRankTile && j < ((len - t0 + 3) & ~3); j += kTopmThreads)
+      s_key[j] = t0 + j < len && masked[beg + t0 + j] ? conf[beg + t0 + j] : NAN;
+  };
+  const bool one_tile = len <= kRankTile;
+  if (one_tile) stage(0);
+
+  int n_masked = 0;
+  Best best{-INFINITY, kNoIndex};
+  for (int i = beg + tid; i < beg + len; i += kTopmThreads) {
+    if (masked[i]) {
+      const float c = conf[i];
+      ++n_masked;
+      if (c > best.c) best = Best{c, i};  // rows ascend per thread: strict > keeps the lowest
+    }
+  }
+  for (int mask = 32; mask >= 1; mask >>= 1) {
+    n_masked += __shfl_xor(n_masked, mask);
+    Best o{__shfl_xor(best.c, mask), __shfl_xor(best.i, mask)};
+    best = best_of(best, o);
+  }
+  if (lane == 0) {
+    s_masked[wave] = n_masked;
+    s_best[wave] = best;
+  }
+  __syncthreads();
+  n_masked = 0;
+  best = Best{-INFINITY, kNoIndex};
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) {
+    n_masked += s_masked[k];
+    best = best_of(best, s_best[k]);
+  }
+
+  // Decide every row, kRankRows per round, without touching the mask flags: lane 0 of a row's four
+  // writes `unmask` and remembers the decision of the first 32 rounds.
+  const bool all = budget >= n_masked;      // every masked row is within the budget
+  const bool ranked = budget > 0 && !all;
+  const int part = tid & (kRankLanes - 1), own = tid / kRankLanes;
+  uint32_t took = 0;
+  int n_pass = 0;
+  for (int r0 = 0, round = 0; r0 < len; r0 += kRankRows, ++round) {
+    const int i = r0 + own;
+    const bool mine = i < len;
+    const float c = mine ? conf[beg + i] : 0.f;
+    const bool mk = mine && masked[beg + i];
+    int rank = 0;
+    if (ranked) {
+      for (int t0 = 0; t0 < len; t0 += kRankTile) {
+        if (!one_tile) {
+          __syncthreads();
+          stage(t0);
+          __syncthreads();
+        }
+        const int tn = min(kRankTile, len - t0);
+        for (int j = 4 * part; j < tn; j += 4 * kRankLanes) {
+          const f32x4 k = *reinterpret_cast<const f32x4*>(s_key + j);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            rank += (k[e] > c || (k[e] == c && t0 + j + e < i)) ? 1 : 0;
+        }
+      }
+      rank += __shfl_xor(rank, 1);
+      rank += __shfl_xor(rank, 2);
+    }
+    const bool take = mk && (c >= tb || all || (ranked && rank < budget));
+    if (part == 0) {
+      n_pass += take ? 1 : 0;
+      if (mine) unmask[beg + i] = take ? 1 : 0;
+      if (round < 32) took |= static_cast<uint32_t>(take) << round;
+    }
+  }
+  for (int mask = 32; mask >= 1; mask >>= 1) n_pass += __shfl_xor(n_pass, mask);
+  if (lane == 0) s_pass[wave] = n_pass;
+  __syncthreads();  // every decision is made before any mask flag changes
+  n_pass = 0;
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) n_pass += s_pass[k];
+  if (n_pass > 0) {
+    if (part == 0)
+      for (int r0 = 0, round = 0; r0 < len; r0 += kRankRows, ++round) {
+        const int i = beg + r0 + own;
+        if (i >= beg + len) break;
+        if (round < 32 ? (took >> round) & 1 : unmask[i] != 0) {
+          tokens[i] = argmax[i];
+          masked[i] = 0;
+        }
+      }
+  } else if (part == 0) {  // fallback: the best masked row, if any
+    for (int i = beg + own; i < beg + len; i += kRankRows)
+      if (i == best.i) {
+        unmask[i] = 1;
+        tokens[i] = argmax[i];
+        masked[i] = 0;
+      }
+  }
+  if (tid == 0) {
+    const int commits = n_pass > 0 ? n_pass : (n_masked > 0 ? 1 : 0);
+    n_commit[b] = commits;
+    resolved[b] = (n_masked - commits == 0) ? 1 : 0;
+  }
+}
+
 // LPS router inputs (Sec. 5.2, Alg. 5), one workgroup per block: the block's mask ratio rho
 // before this step's commit, then per row feat = (kappa, H * inv_ln_v, Delta, rho) and the
 // intra-block position pos = (p_i - p_first) / len, where p is the row's sequence position
@@ -56,7 +186,7 @@ hipError_t unmask_select(int batch, int max_block, const int32_t* cu_block, cons
                          int32_t* tokens, uint8_t* unmask, int32_t* n_commit, uint8_t* resolved,
                          hipStream_t s) {
   (void)max_block;
-  const RuleArgs ra{nullptr, 0.f, 0};
+  const RuleArgs ra{nullptr, 0.f};
   hipLaunchKernelGGL(unmask_kernel<kThreshold>, dim3(batch), dim3(kThreads), 0, s, cu_block,
                      conf, argmax, tau, ra, masked, tokens, unmask, n_commit, resolved);
   return hipGetLastError();
@@ -66,7 +196,7 @@ hipError_t unmask_select_lps(int batch, const int32_t* cu_block, const float* co
                              const int32_t* argmax, const float* tau, const float* p_psi,
                              float tau_psi, uint8_t* masked, int32_t* tokens, uint8_t* unmask,
                              int32_t* n_commit, uint8_t* resolved, hipStream_t s) {
-  const RuleArgs ra{p_psi, tau_psi, 0};
+  const RuleArgs ra{p_psi, tau_psi};
   hipLaunchKernelGGL(unmask_kernel<kUnion>, dim3(batch), dim3(kThreads), 0, s, cu_block, conf,
                      argmax, tau, ra, masked, tokens, unmask, n_commit, resolved);
   return hipGetLastError();
@@ -76,9 +206,8 @@ hipError_t unmask_select_topm(int batch, const int32_t* cu_block, const float* c
                               const int32_t* argmax, const float* tau, int m, uint8_t* masked,
                               int32_t* tokens, uint8_t* unmask, int32_t* n_commit,
                               uint8_t* resolved, hipStream_t s) {
-  const RuleArgs ra{nullptr, 0.f, m};
-  hipLaunchKernelGGL(unmask_kernel<kTopM>, dim3(batch), dim3(kThreads), 0, s, cu_block, conf,
-                     argmax, tau, ra, masked, tokens, unmask, n_commit, resolved);
+  hipLaunchKernelGGL(unmask_topm_kernel, dim3(batch), dim3(kTopmThreads), 0, s, cu_block, conf,
+                     argmax, tau, m, masked, tokens, unmask, n_commit, resolved);
   return hipGetLastError();
 }
 
