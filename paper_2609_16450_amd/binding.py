@@ -160,6 +160,12 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _dev(t: torch.Tensor, name: str, dtype=None, shape=None) -> None:
+    # Every argument of every call passes here, and the small calls are bound by the host: the
+    # common case is decided on the tensor's cheap properties (0.55 us, against 0.93 us for the
+    # comparisons below), and only a refusal goes on to find its reason.
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()
+            and (dtype is None or t.dtype is dtype) and (shape is None or t.shape == shape)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -172,8 +178,16 @@ def _dev(t: torch.Tensor, name: str, dtype=None, shape=None) -> None:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
+# The current device's current stream as a handle, without building a torch.cuda.Stream (0.2
+# against 2 us); None where this torch has no such call.
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+_get_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _get_device is not None and _get_raw_stream is not None:
+            return _get_raw_stream(_get_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
@@ -229,8 +243,11 @@ def _workspace(nbytes: int, ws: Optional[torch.Tensor], device, stream) -> tuple
     if nbytes == 0:
         return (None if ws is None else ws.data_ptr()), (0 if ws is None else ws.numel())
     if ws is None:
-        with torch.cuda.stream(_torch_stream(stream)):
+        if stream is None:  # torch allocates on the current stream by itself
             ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+        else:
+            with torch.cuda.stream(_torch_stream(stream)):
+                ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
     _dev(ws, "ws", torch.uint8)
     return ws.data_ptr(), ws.numel()
 
