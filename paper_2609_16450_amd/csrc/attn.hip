@@ -637,11 +637,23 @@ __global__ __launch_bounds__(kSmallAloneThreads) void attn_small_kernel(AttnPara
 }
 
 // Combine the key-split partials of each (block row, query head), one wavefront per pair.
-template <int D>
+template <int D, int kGroup>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p, int total_block, int batch) {
   const int rh = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (rh >= total_block * p.hq) return;  // uniform per wavefront
-  attn_merge_pair<D>(p, rh, batch, threadIdx.x & 63);
+  attn_merge_pair<D, kGroup>(p, rh, batch, threadIdx.x & 63);
+}
+
+template <int D>
+void launch_merge(const AttnParams& p, int total_block, int batch, hipStream_t s) {
+  const long pairs = static_cast<long>(total_block) * p.hq;
+  const dim3 grid(static_cast<unsigned>((pairs + 3) / 4));
+  if (p.nsplit <= 4)
+    hipLaunchKernelGGL((attn_merge_kernel<D, 4>), grid, dim3(256), 0, s, p, total_block, batch);
+  else if (p.nsplit <= 8)
+    hipLaunchKernelGGL((attn_merge_kernel<D, 8>), grid, dim3(256), 0, s, p, total_block, batch);
+  else
+    hipLaunchKernelGGL((attn_merge_kernel<D, 16>), grid, dim3(256), 0, s, p, total_block, batch);
 }
 
 // fp32 path: one workgroup of eight wavefronts per (sequence, K/V head, 16 query rows), where the
@@ -857,12 +869,10 @@ hipError_t block_attn(bool bf16, bool allow_split, const AttnArgs& a, void* ws, 
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || sp.nsplit == 1 || defer_merge) return e;
-  const long pairs = static_cast<long>(a.total_block) * a.hq;
-  dim3 mgrid(static_cast<unsigned>((pairs + 3) / 4));
   if (a.head_dim == 128)
-    hipLaunchKernelGGL(attn_merge_kernel<128>, mgrid, dim3(256), 0, s, p, a.total_block, a.batch);
+    launch_merge<128>(p, a.total_block, a.batch, s);
   else
-    hipLaunchKernelGGL(attn_merge_kernel<64>, mgrid, dim3(256), 0, s, p, a.total_block, a.batch);
+    launch_merge<64>(p, a.total_block, a.batch, s);
   return hipGetLastError();
 }
 

@@ -78,52 +78,56 @@ inline AttnParams attn_params(const AttnArgs& a, const SplitPlan& sp, void* ws) 
 }
 
 // Combine the key-split partials of pair rh = row * hq + head (one wavefront, lane = lane id):
-// splits merged in index order (max, rescale, sum), output rounded to bf16.
-template <int D>
+// splits merged in index order (max, rescale, sum), output rounded to bf16.  kGroup splits are
+// loaded together.  Bound by latency: the first group's loads do not wait for the search of the
+// row's sequence, whose number of key ranges only decides which of them count (the others are
+// slots of the workspace that no workgroup wrote), and the search is one load per 64 sequences.
+// 380 rows x 16 heads x 64 in 7 ranges: 4.1 us, against 7.9 us with a binary search first, the
+// maxima next and always 16 ranges loaded last.
+template <int D, int kGroup = 16>
 __device__ __forceinline__ void attn_merge_pair(const AttnParams& p, int rh, int batch, int lane) {
-  const int row = rh / p.hq;
-  // sequence of this row: largest b with cu_block[b] <= row (blocks are non-empty here)
-  int lo = 0, hi = batch - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (p.cu_block[mid] <= row) lo = mid; else hi = mid - 1;
-  }
-  const int b = lo;
-  const int n_keys = (p.cu_prefix[b + 1] - p.cu_prefix[b]) + (p.cu_block[b + 1] - p.cu_block[b]) +
-                     (p.cu_suffix ? p.cu_suffix[b + 1] - p.cu_suffix[b] : 0);
-  const int nvalid = min(p.nsplit, (n_keys + p.kps - 1) / p.kps);
-  const size_t base = static_cast<size_t>(rh) * p.nsplit;
-  // kGroup splits at a time, loaded together (clamped index, masked use), combined in index order
-  constexpr int kGroup = 16;
   constexpr int kPer = D / 64;  // values per lane
-  float M = -INFINITY;
-  for (int k0 = 0; k0 < nvalid; k0 += kGroup) {
-    float mk[kGroup];
-#pragma unroll
-    for (int j = 0; j < kGroup; ++j) mk[j] = p.m_part[base + min(k0 + j, nvalid - 1)];
-#pragma unroll
-    for (int j = 0; j < kGroup; ++j)
-      if (k0 + j < nvalid) M = fmaxf(M, mk[j]);
-  }
-  float acc[kPer] = {};
-  float L = 0.f;
-  for (int k0 = 0; k0 < nvalid; k0 += kGroup) {
-    float mk[kGroup], lk[kGroup], ok[kGroup][kPer];
+  const size_t base = static_cast<size_t>(rh) * p.nsplit;
+  float mk[kGroup], lk[kGroup], ok[kGroup][kPer];
+  auto load = [&](int k0) {
 #pragma unroll
     for (int j = 0; j < kGroup; ++j) {
-      const size_t k = base + min(k0 + j, nvalid - 1);
+      const size_t k = base + min(k0 + j, p.nsplit - 1);
       mk[j] = p.m_part[k];
       lk[j] = p.l_part[k];
 #pragma unroll
       for (int e = 0; e < kPer; ++e) ok[j][e] = p.o_part[k * D + lane * kPer + e];
     }
+  };
+  load(0);
+  const int row = rh / p.hq;
+  // sequence of this row: the number of sequences that end at or before it (64 at a time)
+  int b = 0;
+  for (int b0 = 0; b0 < batch; b0 += 64) {
+    const bool before = b0 + lane < batch && p.cu_block[b0 + lane + 1] <= row;
+    const int n = __popcll(__ballot(before));
+    b += n;
+    if (n < 64) break;
+  }
+  const int n_keys = (p.cu_prefix[b + 1] - p.cu_prefix[b]) + (p.cu_block[b + 1] - p.cu_block[b]) +
+                     (p.cu_suffix ? p.cu_suffix[b + 1] - p.cu_suffix[b] : 0);
+  const int nvalid = min(p.nsplit, (n_keys + p.kps - 1) / p.kps);
+  float M = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kGroup; ++j)
+    if (j < nvalid) M = fmaxf(M, mk[j]);
+  for (int k = kGroup; k < nvalid; ++k) M = fmaxf(M, p.m_part[base + k]);
+  float acc[kPer] = {};
+  float L = 0.f;
+  for (int k0 = 0; k0 < nvalid; k0 += kGroup) {
+    if (k0 > 0) load(k0);
 #pragma unroll
     for (int j = 0; j < kGroup; ++j) {
       if (k0 + j >= nvalid) continue;
       const float f = fast_exp2(mk[j] - M);
-      L += f * lk[j];
+      L = fmaf(f, lk[j], L);
 #pragma unroll
-      for (int e = 0; e < kPer; ++e) acc[e] += f * ok[j][e];
+      for (int e = 0; e < kPer; ++e) acc[e] = fmaf(f, ok[j][e], acc[e]);
     }
   }
   const float inv = 1.0f / L;
