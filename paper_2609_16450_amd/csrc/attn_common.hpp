@@ -10,7 +10,15 @@ namespace {
 
 constexpr int kAttnRowsPerWg = 128;  // query rows (position, head-in-group) per workgroup
 constexpr int kAttnKeys = 64;        // keys per LDS stage
-constexpr int kAttnTargetWgs = 512;  // the key split aims at this many workgroups
+// The key split aims at kAttnTargetWgs workgroups, two per compute unit, as long as a range keeps
+// kAttnMinStages stages, and else at kAttnMinWgs: below that, a workgroup's start (its queries and
+// first tiles) and the partials it writes and the merge reads again cost more than the second
+// workgroup brings.  512 against 256 workgroups: 25 against 31 us with 12 stages per range (16
+// sequences, 16 heads x 64, 3000 keys), 42.9 against 41.4 us with 8, 22.0 against 19.3 us with 5,
+// 12.0 against 10.6 us with one.
+constexpr int kAttnMinWgs = 256;
+constexpr int kAttnTargetWgs = 512;
+constexpr int kAttnMinStages = 8;
 
 struct AttnParams {
   const int32_t* cu_block;
@@ -49,8 +57,11 @@ inline SplitPlan split_plan(int batch, int max_block, int max_keys, int hq, int 
       (static_cast<long>(max_block) * group + kAttnRowsPerWg - 1) / kAttnRowsPerWg;
   const long base = row_tiles * hkv * batch;
   const int stages = (max_keys + kAttnKeys - 1) / kAttnKeys;
-  int nsplit = static_cast<int>((kAttnTargetWgs + base - 1) / base);
-  nsplit = max(1, min(nsplit, stages));
+  auto ranges = [&](int target) {
+    return max(1, min(static_cast<int>((target + base - 1) / base), stages));
+  };
+  int nsplit = ranges(kAttnTargetWgs);
+  if (stages < nsplit * kAttnMinStages) nsplit = ranges(kAttnMinWgs);
   const int stages_per = (stages + nsplit - 1) / nsplit;
   const int kps = stages_per * kAttnKeys;
   nsplit = (stages * kAttnKeys + kps - 1) / kps;
