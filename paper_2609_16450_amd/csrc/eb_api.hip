@@ -456,11 +456,7 @@ int32_t eb_decode_step_attn_in_lmhead(const eb_step_desc* d) {
   eb::AttnArgs a{r->batch, T, r->max_block, r->total_prefix, r->max_prefix, r->cu_block,
                  r->cu_prefix, d->hq, d->hkv, d->head_dim, 1.0f, d->q, d->k_blk, d->v_blk,
                  d->k_pre, d->v_pre, d->attn_out};
-  const int n_slices = T > 0 && d->vocab > 0 ? eb::lmhead_num_slices(bf16, T, d->vocab) : 0;
-  return eb::step_finish_fusable(r->max_block, n_slices) &&
-                 eb::lmhead_hosts_attn(bf16, T, d->vocab, a)
-             ? 1
-             : 0;
+  return d->vocab > 0 && eb::lmhead_hosts_attn(bf16, T, d->vocab, a) ? 1 : 0;
 }
 
 size_t eb_decode_step_workspace(const eb_step_desc* d) {
@@ -499,14 +495,13 @@ eb_status eb_decode_step(const eb_step_desc* d, void* ws, size_t ws_bytes, eb_st
                  d->v_blk, d->k_pre, d->v_pre, d->attn_out};
   const size_t attn_ws = eb_block_attn_workspace(d->dtype, r, d->hq, d->hkv, d->head_dim);
   char* lm_ws = static_cast<char*>(ws) + attn_ws;
-  // One epilogue launch (attention split merge + row statistics + unmask) when one workgroup
-  // can reduce a block's LM-head partials; otherwise the three kernels run one after another.
-  const int n_slices = T > 0 ? eb::lmhead_num_slices(bf16, T, d->vocab) : 0;
-  const bool fuse = eb::step_finish_fusable(r->max_block, n_slices);
-
   // Small steps: the attention's workgroups ride in the LM-head launch, behind its slices (its
-  // split merge then happens in the epilogue, which is why this needs `fuse`).
+  // split merge then happens in the epilogue).
   const bool hosted = eb_decode_step_attn_in_lmhead(d) != 0;
+  // One epilogue launch (attention split merge + row statistics + unmask) when one workgroup
+  // quickly reduces a block's LM-head partials; otherwise the three kernels run one after another.
+  const int n_slices = T > 0 ? eb::lmhead_num_slices(bf16, T, d->vocab) : 0;
+  const bool fuse = hosted || eb::step_finish_fusable(r->max_block, n_slices);
 
   hipError_t e = tr ? mark(tr->attn_begin) : hipSuccess;
   if (e == hipSuccess && !hosted) e = eb::block_attn(bf16, true, a, ws, stream, fuse);

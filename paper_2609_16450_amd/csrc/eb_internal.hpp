@@ -47,8 +47,9 @@ hipError_t block_attn(bool bf16, bool allow_split, const AttnArgs& a, void* ws, 
 
 // LM-head partials and the block attention of `a` in one launch: the attention's workgroups are
 // queued behind the LM head's vocabulary slices (key-split partials in attn_ws, merged by
-// step_finish).  Possible when lmhead_hosts_attn(...) holds; the attention then computes
-// exactly what block_attn computes for the same arguments.
+// step_finish, which such a step always takes: its blocks have at most 64 rows x 256 slices).
+// Possible when lmhead_hosts_attn(...) holds; the attention then computes exactly what block_attn
+// computes for the same arguments.
 bool lmhead_hosts_attn(bool bf16, int n_rows, int vocab, const AttnArgs& a);
 hipError_t lmhead_partials_attn(int n_rows, int hidden, int vocab, const void* h, const void* w,
                                 void* ws, const AttnArgs& a, void* attn_ws, hipStream_t s);
@@ -80,9 +81,13 @@ hipError_t lps_features(int batch, const int32_t* cu_block, int vocab, const flo
 // ---- fused step epilogue ---------------------------------------------------------------
 // One launch after block_attn(..., defer_merge = true) and lmhead_partials: merges the attention
 // key splits, combines each row's LM-head partials into conf / entropy / argmax / max_logit,
-// and applies the threshold unmask per block.  Usable when one workgroup can reduce a block's
-// partials (max_block * n_slices <= kFinishMaxPartials).
-constexpr long kFinishMaxPartials = 1L << 16;
+// and applies the threshold unmask per block.  Taken while one workgroup reduces a block's
+// partials quickly (max_block * n_slices <= kFinishMaxPartials); a larger block's partials keep
+// one compute unit busy longer than the separate kernels take, which spread the rows over all of
+// them (whole steps, fused against separate: 217.5 against 211 us with 32 x 494 partials per block,
+// 239 against 208 us with 128 x 494).  A hosted attention's split merge needs it: see
+// lmhead_hosts_attn.
+constexpr long kFinishMaxPartials = 1L << 13;
 bool step_finish_fusable(int max_block, int n_slices);
 hipError_t step_finish(bool bf16, const AttnArgs& a, void* attn_ws, int n_rows, int vocab,
                        const void* lm_ws, float* conf, float* entropy, int32_t* argmax,
