@@ -504,7 +504,8 @@ eb_status eb_decode_step(const eb_step_desc* d, void* ws, size_t ws_bytes, eb_st
   const bool fuse = hosted || eb::step_finish_fusable(r->max_block, n_slices);
 
   hipError_t e = tr ? mark(tr->attn_begin) : hipSuccess;
-  if (e == hipSuccess && !hosted) e = eb::block_attn(bf16, true, a, ws, stream, fuse);
+  if (e == hipSuccess && !hosted && (bf16 || !fuse))  // fp32: in the epilogue launch
+    e = eb::block_attn(bf16, true, a, ws, stream, fuse);
   if (e == hipSuccess && tr) e = mark(tr->attn_end);
   if (e != hipSuccess) return hip_status(e, "step attention launch");
 

@@ -79,8 +79,8 @@ hipError_t lps_features(int batch, const int32_t* cu_block, int vocab, const flo
                         hipStream_t s);
 
 // ---- fused step epilogue ---------------------------------------------------------------
-// One launch after block_attn(..., defer_merge = true) and lmhead_partials: merges the attention
-// key splits, combines each row's LM-head partials into conf / entropy / argmax / max_logit,
+// One launch after block_attn(..., defer_merge = true; bf16 only) and lmhead_partials: merges the
+// attention key splits (bf16) or computes the attention (fp32), combines each row's LM-head partials into conf / entropy / argmax / max_logit,
 // and applies the threshold unmask per block.  Taken while one workgroup reduces a block's
 // partials quickly (max_block * n_slices <= kFinishMaxPartials); a larger block's partials keep
 // one compute unit busy longer than the separate kernels take, which spread the rows over all of

@@ -3,15 +3,19 @@
 //   * merges the attention key-split partials of every (block row, query head) pair, and
 //   * per block: merges each row's LM-head partials into conf, entropy, argmax and top logit
 //     (Alg. 5, confidence of the softmax), then applies the threshold unmask with the
-//     anti-stall fallback (Eq. prelim-update, Alg. 5).
-// The two roles touch disjoint data, so they share one grid: workgroups [0, n_merge) merge
-// attention pairs, the next `batch` workgroups each finish one block.  Each block's rows are
+//     anti-stall fallback (Eq. prelim-update, Alg. 5), and
+//   * in an fp32 step, computes the attention, which depends on neither.
+// The roles touch disjoint data, so they share one grid: workgroups [0, n_merge) merge
+// attention pairs, the next `batch` workgroups each finish one block, those after them run the
+// fp32 attention (a step of a toy model: 14.6 us
+// against 20.5 us with a launch of its own).  Each block's rows are
 // reduced by the block's own workgroup, whose unmask step then reads them back after a barrier
 // (a block of at most 64 rows: from LDS, by one wavefront), so no cross-workgroup ordering is
 // needed.  The arithmetic is that of the separate kernels
 // (same partial merge order, same row statistics, same block step), so the outputs are
 // bit-identical to attention merge + combine + unmask launched one after another.
 #include "attn_common.hpp"
+#include "attn_f32.hpp"
 #include "eb_common.hpp"
 #include "eb_internal.hpp"
 #include "unmask_block.hpp"
@@ -21,10 +25,11 @@ namespace {
 
 constexpr int kFinishThreads = 1024;  // 16 waves: the rows of a block spread over all four SIMDs
 
-// D: attention head dimension of the merge role (unused when n_merge == 0).
-template <int D>
+// D: attention head dimension of the merge role (unused when n_merge == 0) and, with kF32, of the
+// fp32 attention role.
+template <int D, bool kF32>
 __global__ __launch_bounds__(kFinishThreads) void step_finish_kernel(
-    AttnParams ap, int total_block, int batch, int n_merge, const Partial* __restrict__ part,
+    AttnParams ap, AttnParamsF32 ap32, int total_block, int batch, int n_merge, const Partial* __restrict__ part,
     int n_slices, float* __restrict__ conf, float* __restrict__ entropy,
     int32_t* __restrict__ argmax, float* __restrict__ max_logit, const float* __restrict__ tau,
     uint8_t* __restrict__ masked, int32_t* __restrict__ tokens, uint8_t* __restrict__ unmask,
@@ -36,6 +41,12 @@ __global__ __launch_bounds__(kFinishThreads) void step_finish_kernel(
     return;  // whole workgroup: the merge role has no barrier
   }
   const int b = blockIdx.x - n_merge;
+  if constexpr (kF32) {
+    if (b >= batch) {  // whole workgroup
+      attn_f32_role<D, kFinishThreads>(ap32, b - batch);
+      return;
+    }
+  }
   const int beg = ap.cu_block[b], end = ap.cu_block[b + 1];
   // A block of at most 64 rows also leaves its rows' conf and argmax in LDS, and wave 0 then runs
   // the block step alone (one barrier, no reduction across waves; its lanes read their rows' mask
@@ -119,15 +130,18 @@ hipError_t step_finish(bool bf16, const AttnArgs& a, void* attn_ws, int n_rows, 
                     : 0;
   const int n_slices = n_rows > 0 ? lmhead_num_slices(bf16, n_rows, vocab) : 0;
   const Partial* part = static_cast<const Partial*>(lm_ws);
-  const dim3 grid(static_cast<unsigned>(n_merge + a.batch));
-  if (a.head_dim == 64)
-    hipLaunchKernelGGL(step_finish_kernel<64>, grid, dim3(kFinishThreads), 0, s, ap,
-                       a.total_block, a.batch, n_merge, part, n_slices, conf, entropy, argmax,
-                       max_logit, tau, masked, tokens, unmask, n_commit, resolved);
+  const bool f32_attn = !bf16 && a.total_block > 0;
+  const AttnParamsF32 ap32 = f32_attn ? attn_params_f32(a) : AttnParamsF32{};
+  const dim3 grid(static_cast<unsigned>(n_merge + a.batch + (f32_attn ? attn_f32_groups(a) : 0)));
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kFinishThreads), 0, s, ap, ap32, a.total_block, a.batch,
+                       n_merge, part, n_slices, conf, entropy, argmax, max_logit, tau, masked,
+                       tokens, unmask, n_commit, resolved);
+  };
+  if (f32_attn)
+    a.head_dim == 64 ? go(step_finish_kernel<64, true>) : go(step_finish_kernel<128, true>);
   else
-    hipLaunchKernelGGL(step_finish_kernel<128>, grid, dim3(kFinishThreads), 0, s, ap,
-                       a.total_block, a.batch, n_merge, part, n_slices, conf, entropy, argmax,
-                       max_logit, tau, masked, tokens, unmask, n_commit, resolved);
+    a.head_dim == 64 ? go(step_finish_kernel<64, false>) : go(step_finish_kernel<128, false>);
   return hipGetLastError();
 }
 
