@@ -7,9 +7,8 @@
 //   * in an fp32 step, computes the attention, which depends on neither.
 // The roles touch disjoint data, so they share one grid: workgroups [0, n_merge) merge
 // attention pairs, the next `batch` workgroups each finish one block, those after them run the
-// fp32 attention (a step of a toy model: 14.6 us
-// against 20.5 us with a launch of its own).  Each block's rows are
-// reduced by the block's own workgroup, whose unmask step then reads them back after a barrier
+// fp32 attention (a step of a toy model: 14.6 us against 20.5 us with a launch of its own).  Each
+// block's rows are reduced by the block's own workgroup, whose unmask step then reads them back after a barrier
 // (a block of at most 64 rows: from LDS, by one wavefront), so no cross-workgroup ordering is
 // needed.  The arithmetic is that of the separate kernels
 // (same partial merge order, same row statistics, same block step), so the outputs are
