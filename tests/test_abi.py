@@ -119,6 +119,25 @@ def test_workspace_queries():
     assert lib.eb_block_attn_workspace(B.EB_BF16, ctypes.byref(r), 4, 4, 128) == 0
 
 
+@pytest.mark.parametrize("batch,hq,hkv,head_dim,rows,max_keys,ranges", [
+    (1, 32, 32, 128, 32, 544, 9),      # 9 stages of 64 keys, 32 row tiles: one stage per range
+    (1, 32, 32, 128, 32, 2112, 11),    # 33 stages in ranges of 3
+    (8, 16, 4, 64, 64, 1564, 7),       # 64 row tiles: 8 ranges wanted, 25 stages in ranges of 4
+    (4, 28, 4, 128, 100, 2100, 6),     # 96 row tiles: 6 ranges wanted, 33 stages in ranges of 6
+    (64, 28, 4, 128, 256, 4352, 1),    # more row tiles than workgroups wanted
+])
+def test_attention_key_ranges(batch, hq, hkv, head_dim, rows, max_keys, ranges):
+    # The key split aims at 512 workgroups, whatever the stages per range: a plan with fewer ranges
+    # rounds more probabilities to bf16 (only each range's largest is exact).  The workspace holds
+    # head_dim + 2 floats per (row, query head, range).
+    lib = B.load()
+    prefix = max_keys - rows
+    r = B.eb_ragged(batch, batch * rows, rows, batch * prefix, prefix, 0x1000, 0x2000)
+    need = lib.eb_block_attn_workspace(B.EB_BF16, ctypes.byref(r), hq, hkv, head_dim)
+    want = batch * rows * hq * ranges * (head_dim + 2) * 4 if ranges > 1 else 0
+    assert need == (want + 255) // 256 * 256
+
+
 def test_status_strings():
     assert B.eb_status_string(0) == "EB_OK"
     assert B.eb_status_string(3) == "EB_ERR_WORKSPACE"
