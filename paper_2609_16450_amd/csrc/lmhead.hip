@@ -162,22 +162,18 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
   const int nsteps_p = (nsteps + kDepth - 1) / kDepth * kDepth;
   const int nchunks = (hidden + KC - 1) / KC;
 
-  // Workgroups start at different chunks of the hidden dimension and go round.  Rows lie a power of
-  // two apart (8 KB at hidden 4096), so workgroups that all start at column 0 walk the same address
-  // bits together, and where W's pages then favour few memory channels a launch takes up to a
-  // quarter longer: the same head at nine allocations, 32 positions or one, 175-186 us at most of
-  // them but 205, 212 and 233 us at some; with the turn 178-188 us at every one.
-  const int c0 = hidden % KC == 0 ? (wg / 8) % nchunks : 0;
-  auto turned = [](int i, int by, int n) { return i + by < n ? i + by : i + by - n; };
+  // Every workgroup walks the hidden dimension from column 0.  (With starts turned by workgroup the
+  // worst of nine allocations of W, at 32 positions or one, took 188 us instead of 205-233 us, but
+  // a logit's sum then depended on its vocabulary slice: equal rows of W got unequal logits, and
+  // neither the lowest id nor a gap of 0 on a shared maximum held any more.)
   u32x4 buf[kDepth][NL];
   auto issue = [&](int j, int step) {
-    const int st = turned(min(step, nsteps - 1), c0 * kSpc, nsteps);
+    const int st = min(step, nsteps - 1);
 #pragma unroll
     for (int i = 0; i < NL; ++i) buf[j][i] = *reinterpret_cast<const u32x4*>(wp[i] + 64 * st);
   };
   u32x4 hreg[kHPer];
-  auto load_h = [&](int c_) {
-    const int c = turned(c_, c0, nchunks);
+  auto load_h = [&](int c) {
 #pragma unroll
     for (int i = 0; i < kHPer; ++i) {
       const int idx = tid + i * kThreads;
@@ -186,8 +182,7 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
       hreg[i] = *reinterpret_cast<const u32x4*>(h + static_cast<size_t>(row) * hidden + col);
     }
   };
-  auto store_h = [&](int b, int c_) {
-    const int c = turned(c_, c0, nchunks);
+  auto store_h = [&](int b, int c) {
 #pragma unroll
     for (int i = 0; i < kHPer; ++i) {
       const int idx = tid + i * kThreads;

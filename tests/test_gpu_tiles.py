@@ -69,3 +69,26 @@ def test_stream_loads(rows, hidden, vocab):
     np.testing.assert_array_equal(arg.cpu().numpy()[clear], ref["argmax"][clear])
     for got, want in ((conf, "conf"), (ent, "entropy"), (top, "max_logit"), (gap, "top2_gap")):
         np.testing.assert_allclose(got.cpu().numpy(), ref[want], rtol=0, atol=1e-3, err_msg=want)
+
+
+@pytest.mark.parametrize("hidden", [2048, 3584, 4096])
+@pytest.mark.parametrize("rows", [16, 32, 64])
+def test_stream_equal_rows(rows, hidden):
+    """Equal rows of W in any vocabulary slices have bit-identical logits: the lowest id wins and
+    the gap is 0.  Hidden sizes of two to sixteen chunks (3.5 at one position tile), one, two and four position tiles;
+    every position's largest logit is shared by four ids anywhere in 94 slices of 32."""
+    vocab = 3000
+    print(f"equal rows rows={rows} hidden={hidden}", flush=True)
+    rng = np.random.default_rng([rows, hidden])
+    g = torch.Generator(device="cuda").manual_seed(rows + hidden)
+    w = torch.randn(vocab, hidden, generator=g, device="cuda").mul_(hidden ** -0.5).bfloat16()
+    h = torch.randn(rows, hidden, generator=g, device="cuda").bfloat16()
+    ids = rng.permutation(vocab)[:4 * rows].reshape(rows, 4)
+    # z = |h| (8 sigma of a noise logit) for the four, below 6 |h| / sqrt(hidden) for the others
+    u = (h.float() / h.float().norm(dim=1, keepdim=True)).bfloat16()
+    w[torch.from_numpy(ids).cuda().flatten()] = u.repeat_interleave(4, dim=0)
+    conf, ent, gap, top = (torch.empty(rows, device="cuda") for _ in range(4))
+    arg = torch.empty(rows, dtype=torch.int32, device="cuda")
+    eb_lmhead_features(h, w, conf, ent, arg, gap, max_logit=top)
+    np.testing.assert_array_equal(arg.cpu().numpy(), ids.min(axis=1))
+    np.testing.assert_array_equal(gap.cpu().numpy(), np.zeros(rows, np.float32))
