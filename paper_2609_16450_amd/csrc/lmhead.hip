@@ -13,6 +13,7 @@
 #include "attn_small.hpp"
 #include "eb_common.hpp"
 #include "eb_internal.hpp"
+#include "tile_loads.hpp"
 
 namespace eb {
 namespace {
@@ -640,36 +641,33 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
   const bool chain = ns >= 2;  // the last stages of a tile load the next tile's first two
 
   // Load instruction i of this wave covers rows 8 q .. 8 q + 7 of its operand, q = (wave % 2)
-  // kInst + i: lane L fetches one 16-byte chunk of row 8 q + L / 8 into LDS slot L % 8 of the
-  // row, so eight lanes read 128 contiguous bytes, a whole cache line in one L2 request.  (16
-  // rows x 64 bytes per instruction make twice the requests, and the L2 request rate then bounds
-  // the kernel.)  The loads are buffer loads into LDS: a resource per tile and operand in scalar
-  // registers, whose range ends with the operand's last row, so rows past the end read as zero
-  // without a clamp; a byte offset in a vector register, the same for every second instruction;
-  // and the instruction's rows and the stage's columns as the scalar offset.  (Global loads into
-  // LDS would count on the LDS-read counter as well, and the compiler then waits for every
-  // outstanding fragment read before each use of one.)
+  // kInst + i: eight lanes read 128 contiguous bytes of a row, a whole cache line in one L2 request.
+  // (16 rows x 64 bytes per instruction make twice the requests, and the L2 request rate then
+  // bounds the kernel.)  The loads are buffer loads into LDS, whose range ends with the operand's
+  // last row, so rows past the end read as zero without a clamp; tile_loads.hpp has the addresses.
+  // The resource of a 16-row group is scalar arithmetic on the tile's base; the vector offset is the
+  // same for every second instruction.  (Global loads into LDS would count on the LDS-read counter
+  // as well, and the compiler then waits for every outstanding fragment read before each use of
+  // one.)
   const int q0 = (wave & 1) * kInst;
-  // Chunk c of row r sits at place c ^ swz(r) of the LDS row: distinct over the rows that eight
-  // consecutive lanes of a fragment read touch.
-  auto swz = [](int r) { return ((r >> 2) & 3) | ((r & 1) << 2); };
   const uint32_t row_bytes = static_cast<uint32_t>(hidden) * 2;
-  uint32_t voff[2];  // by the instruction's parity (swz depends on row mod 16)
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int row = 8 * i + (lane >> 3);
-    voff[i] = row * row_bytes + 16 * ((lane & 7) ^ swz(row));
-  }
-  auto source = [&](int vt_, int rt_) {
-    const uint16_t* base = kLoadsW ? w + static_cast<size_t>(vt_) * BM * hidden
-                                   : h + static_cast<size_t>(rt_) * BN * hidden;
-    const int rows = kLoadsW ? min(vocab - vt_ * BM, BM) : min(n_rows - rt_ * BN, BN);  // > 0
-    return make_rsrc(base, static_cast<uint32_t>(rows) * row_bytes);
+  const uint32_t voff[2] = {tile_load_voff(0, lane, row_bytes), tile_load_voff(1, lane, row_bytes)};
+  struct Src {
+    const uint8_t* base;
+    int rows;  // of the tile inside the operand, > 0
   };
-  // Load instruction i of stage `stage` of the tile described by rs, into the slot at `slot`.
-  auto load = [&](__amdgpu_buffer_rsrc_t rs, int stage, int slot, int i) {
-    buffer_load_to_lds(rs, smem + slot + (q0 + i) * 1024, voff[i & 1],
-                       stage * (BK * 2) + (q0 + (i & ~1)) * 8 * row_bytes);
+  auto source = [&](int vt_, int rt_) {
+    return kLoadsW ? Src{reinterpret_cast<const uint8_t*>(w + static_cast<size_t>(vt_) * BM * hidden),
+                         min(vocab - vt_ * BM, BM)}
+                   : Src{reinterpret_cast<const uint8_t*>(h + static_cast<size_t>(rt_) * BN * hidden),
+                         min(n_rows - rt_ * BN, BN)};
+  };
+  // Load instruction i of stage `stage` of the tile at p, into the slot at `slot`.
+  auto load = [&](const Src& p, int stage, int slot, int i) {
+    const int row0 = tile_load_row0(q0 + i, p.rows);
+    buffer_load_to_lds(make_rsrc(p.base + static_cast<uint32_t>(row0) * row_bytes,
+                                 tile_load_range(row0, p.rows, row_bytes)),
+                       smem + slot + (q0 + i) * 1024, voff[i & 1], stage * (BK * 2));
   };
   // Fragment f of k step `half` of a stage (f < TM: W block f of this wave, else h block f - TM):
   // lane l reads row rho(l % 16) = 4 (l % 4) + (l % 16) / 4 of the 16-row block, 16-byte chunk
@@ -681,7 +679,7 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
   auto frag = [&](int wslot, int hslot, int half, int f) {
     const int r = f < TM ? wm * kWaveM + f * 16 + rho : wn * kWaveN + (f - TM) * 16 + rho;
     return *reinterpret_cast<const bf16x8*>(smem + (f < TM ? wslot : hslot) + r * kRowB +
-                                            16 * ((4 * half + q4) ^ swz(r)));
+                                            16 * ((4 * half + q4) ^ tile_swizzle(r)));
   };
 
   // LDS offsets of the slots of the current stage and of the next ones, turned once per stage.
@@ -690,7 +688,7 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
   f32x4 acc[TM][TN];
   int s = s0, vt, rt;
   band_tile(s, n_vtiles, n_rtiles, vt, rt);
-  __amdgpu_buffer_rsrc_t src = source(vt, rt), nsrc = src;
+  Src src = source(vt, rt), nsrc = src;
   // Stages 0 and 1 of a tile, then the fragments of (0, a).
   bf16x8 xa[TM], xb[TN], ya[TM], yb[TN];
   auto start = [&]() {
@@ -718,8 +716,8 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
     // One k step: the MFMAs from (ca, cb), the fragments of k step `half` of the stage in slots
     // wslot / hslot into (na, nb), and with do_load stage `stage` of p into the slot at lslot;
     // loads and fragment reads spread over the first three quarters of the MFMAs.
-    auto body = [&](int wslot, int hslot, int half, bool do_load, __amdgpu_buffer_rsrc_t p,
-                    int stage, int lslot, const bf16x8 (&ca)[TM], const bf16x8 (&cb)[TN],
+    auto body = [&](int wslot, int hslot, int half, bool do_load, const Src& p, int stage,
+                    int lslot, const bf16x8 (&ca)[TM], const bf16x8 (&cb)[TN],
                     bf16x8 (&na)[TM], bf16x8 (&nb)[TN]) {
       auto load_at = [](int l) { return (6 * l + 1) * kMfmas / (8 * kInst); };
       auto read_at = [](int f) { return (6 * (f / 2) + 3 + 2 * (f & 1)) * kMfmas / (4 * kReads); };
@@ -739,7 +737,7 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
       static_assert(kInst <= kMfmas * 7 / 8, "every load finds its MFMA");
     };
     // One stage; stage `stage` of p is loaded on the way.
-    auto run_stage = [&](__amdgpu_buffer_rsrc_t p, int stage) {
+    auto run_stage = [&](const Src& p, int stage) {
       body(w0, h0, 1, kLoadsW, p, stage, w2, xa, xb, ya, yb);
       // the next stage has landed (W: all but the stage just issued)
       wait_vm_lds_and_barrier<kLoadsW ? kInst : 0>();
@@ -760,7 +758,7 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
     // stage per tile, this tile's last stage again, never read).
     int st = 0;
     for (; st + 2 < ns; ++st) run_stage(src, st + 2);
-    const __amdgpu_buffer_rsrc_t tsrc = pre ? nsrc : src;
+    const Src tsrc{pre ? nsrc.base : src.base, pre ? nsrc.rows : src.rows};
     for (; st < ns; ++st) run_stage(tsrc, pre ? st + 2 - ns : ns - 1);
     if (!pre) wait_vm_lds_and_barrier<0>();  // no DMA in flight
     acc_fence_out(acc);  // every MFMA has written its accumulator before the epilogue reads it
