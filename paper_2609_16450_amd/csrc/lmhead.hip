@@ -41,22 +41,24 @@ constexpr int kStreamGroups = EB_STREAM_GROUPS;  // workgroups (256: one per com
 // The streaming kernel uses 16x16x32 MFMA tiles (mfma16; 32x32x16 tiles measured 4.65 TB/s at best
 // against 5.4).  A lane of the A operand holds 8 k-values of row l % 16, so loads straight into
 // that layout would read 16 rows x 64 bytes, half a cache line per row.  Instead a k-step is 64
-// columns of a 16-row tile in two loads of 8 rows x 128 bytes: lane l loads 16-byte chunk l / 8 of
-// row l % 8 (v0) and of row 8 + l % 8 (v1).  line_to_frag exchanges v0 and v1 between lanes l and
-// l ^ 8, after which lane l holds row l % 16 in both, chunk 2 (l / 16) in the first and
-// 2 (l / 16) + 1 in the second: the A operands of two MFMAs whose contraction indices are the even
-// and the odd chunks of the step.  h is read from LDS in the same order.
-__device__ __forceinline__ void line_to_frag(const u32x4& v0, const u32x4& v1, bf16x8& even,
-                                             bf16x8& odd) {
+// columns of a 16-row tile in two loads of 8 rows x 128 bytes: lane l loads 16-byte chunk
+// line_chunk(l) of row l % 8 (v0) and of row 8 + l % 8 (v1).  line_to_frag exchanges v0 and v1
+// between lanes l and l ^ 8, after which lane l holds row l % 16 in both, chunk l / 16 in the first
+// and 4 + l / 16 in the second: the A operands of the MFMAs of the step's first and last 32 columns.
+// A logit is thus summed in the order of its columns, as in the tile kernel, so a position's logits
+// do not depend on how many positions the call has.
+__device__ __forceinline__ int line_chunk(int lane) { return (lane >> 4) + 4 * ((lane >> 3) & 1); }
+__device__ __forceinline__ void line_to_frag(const u32x4& v0, const u32x4& v1, bf16x8& first,
+                                             bf16x8& last) {
   constexpr int kRor8 = 0x128;  // DPP row_ror:8: from the lane 8 away in the row of 16
-  u32x4 e, o;
+  u32x4 f, l;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    e[i] = __builtin_amdgcn_update_dpp(v0[i], v1[i], kRor8, 0xf, 0xc, false);  // lanes 8..15
-    o[i] = __builtin_amdgcn_update_dpp(v1[i], v0[i], kRor8, 0xf, 0x3, false);  // lanes 0..7
+    f[i] = __builtin_amdgcn_update_dpp(v0[i], v1[i], kRor8, 0xf, 0xc, false);  // lanes 8..15
+    l[i] = __builtin_amdgcn_update_dpp(v1[i], v0[i], kRor8, 0xf, 0x3, false);  // lanes 0..7
   }
-  even = __builtin_bit_cast(bf16x8, e);
-  odd = __builtin_bit_cast(bf16x8, o);
+  first = __builtin_bit_cast(bf16x8, f);
+  last = __builtin_bit_cast(bf16x8, l);
 }
 
 // Second-largest logit (with multiplicity) of the union of two sets whose largest values are
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
     const int row = min(wb + i * 8 + (lane & 7), wlast);
-    wp[i] = w + static_cast<size_t>(row) * hidden + 8 * (lane >> 3);
+    wp[i] = w + static_cast<size_t>(row) * hidden + 8 * line_chunk(lane);
   }
   const int nsteps = hidden / 64;
   const int nsteps_p = (nsteps + kDepth - 1) / kDepth * kDepth;
@@ -207,7 +209,7 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
   if (nchunks > 1) load_h(1);
 
   auto consume = [&](int g, int j) {
-    const uint16_t* hb = hs[(g / kSpc) & 1] + (g % kSpc) * 64 + 16 * grp + 64 * j;
+    const uint16_t* hb = hs[(g / kSpc) & 1] + (g % kSpc) * 64 + 8 * grp + 64 * j;
     bf16x8 a[TM][2];
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)  // (upper rows that are not there repeat the lower ones)
@@ -216,7 +218,7 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(hb + (nt * 16 + l16) * kPitch + 8 * i);
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(hb + (nt * 16 + l16) * kPitch + 32 * i);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) acc[tm][nt] = mfma16(a[tm][i], b, acc[tm][nt]);
       }

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle
-from paper_2609_16450_amd import eb_lmhead_features
+from paper_2609_16450_amd import eb_lmhead_confidence, eb_lmhead_features
 from workloads import bf16_bits_to_f32, f32_to_bf16_bits
 
 pytestmark = pytest.mark.gpu
@@ -92,3 +92,23 @@ def test_stream_equal_rows(rows, hidden):
     eb_lmhead_features(h, w, conf, ent, arg, gap, max_logit=top)
     np.testing.assert_array_equal(arg.cpu().numpy(), ids.min(axis=1))
     np.testing.assert_array_equal(gap.cpu().numpy(), np.zeros(rows, np.float32))
+
+
+@pytest.mark.parametrize("hidden", [64, 1088, 3584, 4096])
+def test_logits_do_not_depend_on_the_row_count(hidden):
+    """A logit is summed in the order of its columns by every bf16 kernel: a position's largest logit
+    and its id are the same bits alone, with one, two and four position tiles of the streaming kernel
+    and in the tile kernel."""
+    print(f"row counts hidden={hidden}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(hidden)
+    w = torch.randn(5000, hidden, generator=g, device="cuda").mul_(hidden ** -0.5).bfloat16()
+    h = torch.randn(300, hidden, generator=g, device="cuda").bfloat16()
+    got = {}
+    for rows in (300, 65, 64, 33, 17, 16, 1):
+        conf, ent, top = (torch.empty(rows, device="cuda") for _ in range(3))
+        arg = torch.empty(rows, dtype=torch.int32, device="cuda")
+        eb_lmhead_confidence(h[:rows], w, conf, ent, arg, max_logit=top)
+        got[rows] = top, arg
+    for rows, (top, arg) in got.items():
+        assert torch.equal(top, got[300][0][:rows]), rows
+        assert torch.equal(arg, got[300][1][:rows]), rows
