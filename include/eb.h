@@ -143,7 +143,8 @@ eb_status eb_block_attn_dual(eb_dtype dt, const eb_ragged* r, const eb_suffix* s
  *
  * Requires n_rows >= 0, vocab >= 1, hidden >= 1; EB_BF16 also needs hidden % 64 == 0.
  * ws: at least eb_lmhead_workspace(...) bytes of device memory, contents ignored; it holds
- * per-(row, vocabulary slice) partial reductions merged in a fixed order.
+ * per-(row, vocabulary slice) partial reductions merged in a fixed order.  In EB_F32 the size never
+ * decreases as n_rows grows, so a workspace for the largest call serves every smaller one.
  * ------------------------------------------------------------------------------------- */
 size_t eb_lmhead_workspace(eb_dtype dt, int n_rows, int hidden, int vocab);
 eb_status eb_lmhead_confidence(eb_dtype dt, int n_rows, int hidden, int vocab, const void* h,

@@ -911,11 +911,14 @@ constexpr int kF32Waves = 4;
 constexpr int kF32NT = 2;  // 16-position tiles per workgroup
 
 // Rows per slice.  Slices of 64 rows make four times the workgroups and partials: only where
-// 256-row slices would give fewer workgroups than compute units, so the partials stay few.
+// 256-row slices would give fewer workgroups than compute units, so the partials stay few.  That is
+// up to f32_small_slice_rows position rows.
+int f32_small_slice_rows(int vocab) {
+  const int slices = (vocab + kF32SliceRows - 1) / kF32SliceRows;
+  return 255 / slices * 16 * kF32NT;
+}
 int f32_slice_rows(int n_rows, int vocab) {
-  const long groups = static_cast<long>((vocab + kF32SliceRows - 1) / kF32SliceRows) *
-                      ((n_rows + 16 * kF32NT - 1) / (16 * kF32NT));
-  return groups < 256 ? kF32SmallSliceRows : kF32SliceRows;
+  return n_rows <= f32_small_slice_rows(vocab) ? kF32SmallSliceRows : kF32SliceRows;
 }
 
 // Four floats of row `row` from column `col`; columns from `n` on are zero.
@@ -1085,9 +1088,15 @@ static size_t lmhead_part_bytes(bool bf16, int n_rows, int vocab) {
 }
 
 size_t lmhead_ws_bytes(bool bf16, int n_rows, int vocab, bool top2) {
-  size_t b = lmhead_part_bytes(bf16, n_rows, vocab);
-  if (top2) b += static_cast<size_t>(n_rows) * lmhead_num_slices(bf16, n_rows, vocab) * 4;
-  return b;
+  auto bytes = [&](int rows) {
+    size_t b = lmhead_part_bytes(bf16, rows, vocab);
+    if (top2) b += static_cast<size_t>(rows) * lmhead_num_slices(bf16, rows, vocab) * 4;
+    return b;
+  };
+  // fp32: also enough for every smaller row count, whose slices may be four times as many, so that a
+  // workspace made for the largest call serves the others
+  return bf16 ? bytes(n_rows)
+              : max(bytes(n_rows), bytes(min(n_rows, f32_small_slice_rows(vocab))));
 }
 
 hipError_t lmhead_partials(bool bf16, int n_rows, int hidden, int vocab, const void* h,

@@ -119,6 +119,23 @@ def test_workspace_queries():
     assert lib.eb_block_attn_workspace(B.EB_BF16, ctypes.byref(r), 4, 4, 128) == 0
 
 
+@pytest.mark.parametrize("vocab", [1, 64, 300, 2048, 8192, 65281, 70001, 126464])
+def test_f32_lmhead_workspace_grows_with_the_rows(vocab):
+    # a workspace made for the largest fp32 call serves every smaller one
+    lib = B.load()
+    d = B.eb_step_desc()
+    d.dtype, d.hq, d.hkv, d.head_dim, d.hidden, d.vocab = B.EB_F32, 4, 4, 64, 256, vocab
+
+    def step(n):
+        d.ragged = B.eb_ragged(1, n, n, 0, 0, 0x1000, 0x2000)
+        return lib.eb_decode_step_workspace(ctypes.byref(d))
+
+    for size in (lambda n: lib.eb_lmhead_workspace(B.EB_F32, n, 256, vocab),
+                 lambda n: lib.eb_lmhead_features_workspace(B.EB_F32, n, 256, vocab), step):
+        sizes = [size(n) for n in range(9000)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
 @pytest.mark.parametrize("batch,hq,hkv,head_dim,rows,max_keys,ranges", [
     (1, 32, 32, 128, 32, 544, 9),      # 9 stages of 64 keys, 32 row tiles: one stage per range
     (1, 32, 32, 128, 32, 2112, 11),    # 33 stages in ranges of 3
