@@ -659,7 +659,8 @@ void launch_merge(const AttnParams& p, int total_block, int batch, hipStream_t s
 
 template <int D>
 __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParamsF32 p) {
-  attn_f32_role<D, kF32Threads>(p, blockIdx.x);
+  attn_f32_role<D, kF32Threads>(p, blockIdx.x % p.tiles, blockIdx.x / p.tiles % p.hkv,
+                                blockIdx.x / p.tiles / p.hkv);
 }
 
 // attn_bf16_d128_kernel addresses a key row by a 32-bit byte offset from its segment's first

@@ -7,9 +7,10 @@
 namespace eb {
 namespace {
 
-// fp32 attention, as the role of a workgroup: a kernel of its own (attn_f32_kernel) or, in a step,
-// the last workgroups of the epilogue launch, which saves the step a launch.  One workgroup of eight wavefronts per (sequence, K/V head, 16 query rows), where the
-// query rows are the (position, head-in-group) pairs.  Wave v takes the 16-key chunks v, v + 8,
+// fp32 attention, as the role of a workgroup: a kernel of its own (attn_f32_kernel) or, in a small
+// step, the last workgroups of the epilogue launch, which saves the step a launch.  One workgroup of
+// eight wavefronts per (sequence, K/V head, 16 query rows), where the query rows are the (position,
+// head-in-group) pairs.  Wave v takes the 16-key chunks v, v + 8,
 // ... of the sequence's keys with an online softmax of its own, and the eight partial results are
 // merged through LDS.  Scores are formed transposed, S^T = K Q^T, by 16x16x4 fp32 MFMAs (fp32
 // multiply-adds): lane l owns query l % 16 and holds keys 4 (l / 16) + r of the chunk, which are
@@ -40,7 +41,7 @@ constexpr int kF32Keys = 16;  // keys per chunk
 
 constexpr int kF32Threads = kF32Waves * 64;
 
-// Workgroups of the role, one per (sequence, K/V head, tile of query rows), and its parameters.
+// Workgroups of the role, one per (tile of query rows, K/V head, sequence), and its parameters.
 inline long attn_f32_tiles(const AttnArgs& a) {
   return (static_cast<long>(a.max_block) * (a.hq / a.hkv) + kF32Rows - 1) / kF32Rows;
 }
@@ -53,16 +54,15 @@ inline AttnParamsF32 attn_params_f32(const AttnArgs& a) {
                        a.cu_suffix, f(a.k_suf), f(a.v_suf)};
 }
 
-// Role of workgroup `unit`.  Every thread of the workgroup calls it; waves past kF32Waves only help
+// Role of the workgroup of tile `tile`, K/V head g and sequence b.  Every thread of the workgroup calls it; waves past kF32Waves only help
 // with the final merge, so the results do not depend on the workgroup's size.
 template <int D, int kThreads>
-__device__ __forceinline__ void attn_f32_role(const AttnParamsF32& p, int unit) {
+__device__ __forceinline__ void attn_f32_role(const AttnParamsF32& p, int tile, int g, int b) {
   constexpr int kChunks = D / 16;  // 16-column chunks of the head dimension
   constexpr int kPitch = D + 4;    // LDS row pitch of a partial O
   __shared__ __attribute__((aligned(16))) float s_o[kF32Waves][kF32Rows * kPitch];
   __shared__ float s_m[kF32Waves][kF32Rows], s_l[kF32Waves][kF32Rows];
-  const int row0 = unit % p.tiles * kF32Rows;
-  const int g = unit / p.tiles % p.hkv, b = unit / p.tiles / p.hkv;
+  const int row0 = tile * kF32Rows;
   const int bbeg = p.cu_block[b];
   const int len = p.cu_block[b + 1] - bbeg;
   const int G = p.group;

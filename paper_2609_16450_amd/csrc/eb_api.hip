@@ -502,9 +502,10 @@ eb_status eb_decode_step(const eb_step_desc* d, void* ws, size_t ws_bytes, eb_st
   // quickly reduces a block's LM-head partials; otherwise the three kernels run one after another.
   const int n_slices = T > 0 ? eb::lmhead_num_slices(bf16, T, d->vocab) : 0;
   const bool fuse = hosted || eb::step_finish_fusable(r->max_block, n_slices);
+  const bool attn_f32 = fuse && eb::step_finish_hosts_attn(bf16, a);  // in the epilogue launch
 
   hipError_t e = tr ? mark(tr->attn_begin) : hipSuccess;
-  if (e == hipSuccess && !hosted && (bf16 || !fuse))  // fp32: in the epilogue launch
+  if (e == hipSuccess && !hosted && !attn_f32)
     e = eb::block_attn(bf16, true, a, ws, stream, fuse);
   if (e == hipSuccess && tr) e = mark(tr->attn_end);
   if (e != hipSuccess) return hip_status(e, "step attention launch");
@@ -519,9 +520,9 @@ eb_status eb_decode_step(const eb_step_desc* d, void* ws, size_t ws_bytes, eb_st
   if (tr) e = mark(tr->select_begin);
   if (fuse) {
     if (e == hipSuccess)
-      e = eb::step_finish(bf16, a, ws, T, d->vocab, lm_ws, d->conf, d->entropy_nats, d->argmax,
-                          d->max_logit, d->tau, d->masked, d->tokens, d->unmask, d->n_commit,
-                          d->resolved, stream);
+      e = eb::step_finish(bf16, attn_f32, a, ws, T, d->vocab, lm_ws, d->conf, d->entropy_nats,
+                          d->argmax, d->max_logit, d->tau, d->masked, d->tokens, d->unmask,
+                          d->n_commit, d->resolved, stream);
   } else {
     if (e == hipSuccess && T > 0)
       e = eb::lmhead_combine(bf16, T, d->vocab, lm_ws, d->conf, d->entropy_nats, d->argmax,

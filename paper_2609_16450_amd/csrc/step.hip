@@ -4,15 +4,14 @@
 //   * per block: merges each row's LM-head partials into conf, entropy, argmax and top logit
 //     (Alg. 5, confidence of the softmax), then applies the threshold unmask with the
 //     anti-stall fallback (Eq. prelim-update, Alg. 5), and
-//   * in an fp32 step, computes the attention, which depends on neither.
+//   * in a small fp32 step, computes the attention, which depends on neither.
 // The roles touch disjoint data, so they share one grid: workgroups [0, n_merge) merge
 // attention pairs, the next `batch` workgroups each finish one block, those after them run the
-// fp32 attention (a step of a toy model: 14.6 us against 20.5 us with a launch of its own).  Each
-// block's rows are reduced by the block's own workgroup, whose unmask step then reads them back after a barrier
-// (a block of at most 64 rows: from LDS, by one wavefront), so no cross-workgroup ordering is
-// needed.  The arithmetic is that of the separate kernels
-// (same partial merge order, same row statistics, same block step), so the outputs are
-// bit-identical to attention merge + combine + unmask launched one after another.
+// fp32 attention (step_finish_hosts_attn).  Each block's rows are reduced by the block's own
+// workgroup, whose unmask step then reads them back after a barrier (a block of at most 64 rows:
+// from LDS, by one wavefront), so no cross-workgroup ordering is needed.  The arithmetic is that of
+// the separate kernels (same partial merge order, same row statistics, same block step), so the
+// outputs are bit-identical to attention merge + combine + unmask launched one after another.
 #include "attn_common.hpp"
 #include "attn_f32.hpp"
 #include "eb_common.hpp"
@@ -28,11 +27,11 @@ constexpr int kFinishThreads = 1024;  // 16 waves: the rows of a block spread ov
 // fp32 attention role.
 template <int D, bool kF32>
 __global__ __launch_bounds__(kFinishThreads) void step_finish_kernel(
-    AttnParams ap, AttnParamsF32 ap32, int total_block, int batch, int n_merge, const Partial* __restrict__ part,
-    int n_slices, float* __restrict__ conf, float* __restrict__ entropy,
-    int32_t* __restrict__ argmax, float* __restrict__ max_logit, const float* __restrict__ tau,
-    uint8_t* __restrict__ masked, int32_t* __restrict__ tokens, uint8_t* __restrict__ unmask,
-    int32_t* __restrict__ n_commit, uint8_t* __restrict__ resolved) {
+    AttnParams ap, AttnParamsF32 ap32, int total_block, int batch, int n_merge,
+    const Partial* __restrict__ part, int n_slices, float* __restrict__ conf,
+    float* __restrict__ entropy, int32_t* __restrict__ argmax, float* __restrict__ max_logit,
+    const float* __restrict__ tau, uint8_t* __restrict__ masked, int32_t* __restrict__ tokens,
+    uint8_t* __restrict__ unmask, int32_t* __restrict__ n_commit, uint8_t* __restrict__ resolved) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (static_cast<int>(blockIdx.x) < n_merge) {
     const int rh = blockIdx.x * (kFinishThreads / 64) + wave;
@@ -42,7 +41,8 @@ __global__ __launch_bounds__(kFinishThreads) void step_finish_kernel(
   const int b = blockIdx.x - n_merge;
   if constexpr (kF32) {
     if (b >= batch) {  // whole workgroup
-      attn_f32_role<D, kFinishThreads>(ap32, b - batch);
+      const int tile = (b - batch) % ap32.tiles, gb = (b - batch) / ap32.tiles;
+      attn_f32_role<D, kFinishThreads>(ap32, tile, gb % ap32.hkv, gb / ap32.hkv);
       return;
     }
   }
@@ -115,7 +115,17 @@ bool step_finish_fusable(int max_block, int n_slices) {
   return static_cast<long>(max_block) * n_slices <= kFinishMaxPartials;
 }
 
-hipError_t step_finish(bool bf16, const AttnArgs& a, void* attn_ws, int n_rows, int vocab,
+// The fp32 attention rides in the epilogue launch while it has at most one workgroup per compute
+// unit.  That saves a launch: a step of a toy model takes 14.6 us against 21.1 us with a launch of
+// its own, one of 256 attention workgroups over 320 to 4000 keys 3 to 27% less.  A workgroup here
+// has twice the waves that the attention needs and fills a compute unit, which holds two of the
+// attention kernel's own: 512 to 2048 workgroups took 45 against 42 us, 270 against 190 us and 1239
+// against 793 us (head dimension 128), at 64 up to a fifth more.
+bool step_finish_hosts_attn(bool bf16, const AttnArgs& a) {
+  return !bf16 && a.total_block > 0 && attn_f32_groups(a) <= 256;
+}
+
+hipError_t step_finish(bool bf16, bool attn_f32, const AttnArgs& a, void* attn_ws, int n_rows, int vocab,
                        const void* lm_ws, float* conf, float* entropy, int32_t* argmax,
                        float* max_logit, const float* tau, uint8_t* masked, int32_t* tokens,
                        uint8_t* unmask, int32_t* n_commit, uint8_t* resolved, hipStream_t s) {
@@ -129,15 +139,14 @@ hipError_t step_finish(bool bf16, const AttnArgs& a, void* attn_ws, int n_rows, 
                     : 0;
   const int n_slices = n_rows > 0 ? lmhead_num_slices(bf16, n_rows, vocab) : 0;
   const Partial* part = static_cast<const Partial*>(lm_ws);
-  const bool f32_attn = !bf16 && a.total_block > 0;
-  const AttnParamsF32 ap32 = f32_attn ? attn_params_f32(a) : AttnParamsF32{};
-  const dim3 grid(static_cast<unsigned>(n_merge + a.batch + (f32_attn ? attn_f32_groups(a) : 0)));
+  const AttnParamsF32 ap32 = attn_f32 ? attn_params_f32(a) : AttnParamsF32{};
+  const dim3 grid(static_cast<unsigned>(n_merge + a.batch + (attn_f32 ? attn_f32_groups(a) : 0)));
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(kFinishThreads), 0, s, ap, ap32, a.total_block, a.batch,
                        n_merge, part, n_slices, conf, entropy, argmax, max_logit, tau, masked,
                        tokens, unmask, n_commit, resolved);
   };
-  if (f32_attn)
+  if (attn_f32)
     a.head_dim == 64 ? go(step_finish_kernel<64, true>) : go(step_finish_kernel<128, true>);
   else
     a.head_dim == 64 ? go(step_finish_kernel<64, false>) : go(step_finish_kernel<128, false>);

@@ -4,8 +4,8 @@ import pytest
 import torch
 
 import oracle
-from paper_2609_16450_amd import (eb_block_attn, eb_decode_step, eb_lmhead_confidence,
-                                  eb_unmask_select)
+from paper_2609_16450_amd import (Ragged, StepBuffers, eb_block_attn, eb_decode_step,
+                                  eb_lmhead_confidence, eb_unmask_select)
 from paper_2609_16450_amd.device_case import DeviceStep
 from workloads import bf16_bits_to_f32, custom_config, make_step
 
@@ -50,3 +50,49 @@ def test_epilogue_rule(rows, vocab):
     for k in ("attn_out", "conf", "entropy", "argmax", "max_logit", "masked", "tokens", "unmask",
               "n_commit", "resolved"):
         assert torch.equal(getattr(a, k), getattr(b, k)), k
+
+
+# fp32 steps, bit for bit against the separate entry points.  The attention is in the epilogue launch
+# with up to 256 workgroups (tiles of 16 query rows, K/V heads, sequences), when that is one launch:
+# 70001 entries are 274 slices, so a block of 29 rows has 7946 partials (one launch) and one of 30
+# rows 8220 (three kernels).  Empty blocks, and both head dimensions in the epilogue.
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("lens,hq,hkv,vocab", [
+    ((20, 0, 7, 33), 4, 2, 2048), ((0, 1, 5, 0), 3, 1, 300),
+    ((16,) * 8, 32, 32, 999), ((16,) * 8 + (1,), 32, 32, 999),  # 256 workgroups, 288
+    ((29, 3), 2, 2, 70001), ((30, 3), 2, 2, 70001)])
+def test_fp32_step(lens, hq, hkv, vocab, head_dim):
+    print(f"fp32 step blocks={lens} hq={hq} hkv={hkv} V={vocab} D={head_dim}", flush=True)
+    T, B, hidden = sum(lens), len(lens), 100
+    prefix = [37 * b % 150 for b in range(B)]
+    g = torch.Generator(device="cuda").manual_seed(T + vocab)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+
+    q, h, w = normal(T, hq, head_dim), normal(T, hidden), normal(vocab, hidden)
+    kv = [normal(n, hkv, head_dim) for n in (T, T, sum(prefix), sum(prefix))]
+    masked0 = (torch.rand(T, generator=g, device="cuda") < 0.7).to(torch.uint8)
+    tau = torch.full((B,), 0.5, device="cuda")
+    r = Ragged.from_lengths(list(lens), prefix)
+    got = []
+    for step in (True, False):
+        f32 = [torch.full((T,), -1.0, device="cuda") for _ in range(3)]
+        i32 = [torch.full((n,), -1, dtype=torch.int32, device="cuda") for n in (T, T, B)]
+        u8 = [torch.full((n,), 9, dtype=torch.uint8, device="cuda") for n in (T, B)]
+        (conf, ent, top), (arg, tokens, n_commit), (unmask, resolved) = f32, i32, u8
+        out, masked = torch.full_like(q, 7.0), masked0.clone()
+        if step:
+            eb_decode_step(StepBuffers(r, q, *kv, out, h, w, conf, ent, arg, tau, masked, tokens,
+                                       unmask, n_commit, resolved, max_logit=top))
+        else:
+            eb_block_attn(r, q, *kv, out)
+            eb_lmhead_confidence(h, w, conf, ent, arg, top)
+            eb_unmask_select(r, conf, arg, tau, masked, tokens, unmask, n_commit, resolved)
+        got.append([out, masked, *f32, *i32, *u8])
+    for i, (a, b) in enumerate(zip(*got)):
+        assert torch.equal(a, b), i
+    ref = oracle.block_attention(q.cpu().numpy(), *(x.cpu().numpy() for x in kv),
+                                 r.cu_block.cpu().numpy(), r.cu_prefix.cpu().numpy(), hq, hkv)
+    # scores of size |q||k| / sqrt(d) < 16 off by some 128 2^-24 16 / sqrt(128): 1e-5 in a weight
+    np.testing.assert_allclose(got[0][0].cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
