@@ -284,7 +284,8 @@ eb_status eb_lbs_select(int32_t n_seq, int32_t window, const uint8_t* masked,
  * merge of the LM-head partials and the unmask run as one epilogue launch (unless a block's
  * rows times the LM head's vocabulary slices exceed 8192, when they run separately; the small
  * steps below always have the one launch; in fp32 that launch computes the attention as well, as
- * long as it has at most 256 tiles of 16 query rows over all sequences and K/V heads),
+ * long as it has at most 256 tiles of 16 query rows over all sequences and K/V heads and no trace
+ * event asks for its time),
  * and in small bf16 steps (at most 64 block rows, at most 256 query rows per sequence and K/V head,
  * head_dim 64 or 128, an LM head streamed by 16-wave workgroups) the attention's workgroups are
  * queued behind the LM head's in the same launch, which starts them as the LM head's
@@ -304,8 +305,8 @@ typedef struct {
                                           when the attention shares the LM-head launch */
   eb_event_t lmhead_begin, lmhead_end; /* around the fused LM-head kernel (without its merge),
                                           including the attention when it shares the launch */
-  eb_event_t select_begin, select_end; /* around the epilogue: split merges and unmask, in fp32
-                                          also the attention when the epilogue is one launch */
+  eb_event_t select_begin, select_end; /* around the epilogue: split merges and unmask (in fp32
+                                          also a small attention, unless an attn_* event is set) */
 } eb_step_trace;
 
 typedef struct {

@@ -502,7 +502,9 @@ eb_status eb_decode_step(const eb_step_desc* d, void* ws, size_t ws_bytes, eb_st
   // quickly reduces a block's LM-head partials; otherwise the three kernels run one after another.
   const int n_slices = T > 0 ? eb::lmhead_num_slices(bf16, T, d->vocab) : 0;
   const bool fuse = hosted || eb::step_finish_fusable(r->max_block, n_slices);
-  const bool attn_f32 = fuse && eb::step_finish_hosts_attn(bf16, a);  // in the epilogue launch
+  // The fp32 attention in the epilogue launch, unless the caller times it.
+  const bool attn_f32 = fuse && eb::step_finish_hosts_attn(bf16, a) &&
+                        !(tr && (tr->attn_begin || tr->attn_end));
 
   hipError_t e = tr ? mark(tr->attn_begin) : hipSuccess;
   if (e == hipSuccess && !hosted && !attn_f32)

@@ -6,6 +6,7 @@ import torch
 import oracle
 from paper_2609_16450_amd import (Ragged, StepBuffers, eb_block_attn, eb_decode_step,
                                   eb_lmhead_confidence, eb_unmask_select)
+from paper_2609_16450_amd.binding import eb_step_trace
 from paper_2609_16450_amd.device_case import DeviceStep
 from workloads import bf16_bits_to_f32, custom_config, make_step
 
@@ -96,3 +97,20 @@ def test_fp32_step(lens, hq, hkv, vocab, head_dim):
                                  r.cu_block.cpu().numpy(), r.cu_prefix.cpu().numpy(), hq, hkv)
     # scores of size |q||k| / sqrt(d) < 16 off by some 128 2^-24 16 / sqrt(128): 1e-5 in a weight
     np.testing.assert_allclose(got[0][0].cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
+
+
+def test_traced_fp32_step_times_its_attention():
+    """The attn_* events of a traced fp32 step bracket the attention, and the step's outputs are those
+    of an untraced one.  4096 keys: some 200 us of attention for an idle bracket of under 20 us."""
+    case = make_step(custom_config(seed=5, hidden=64, vocab=300, head_dim=128, dtype="f32",
+                                   block_len=("fixed", 32), prefix_len=("fixed", 4064)))
+    a, b = DeviceStep(case), DeviceStep(case)
+    eb_decode_step(a.buffers)
+    begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    for e in (begin, end):
+        e.record()  # creates the event
+    eb_decode_step(b.buffers, trace=eb_step_trace(begin.cuda_event, end.cuda_event, 0, 0, 0, 0))
+    torch.cuda.synchronize()
+    assert begin.elapsed_time(end) > 0.05
+    for k in ("attn_out", "conf", "entropy", "argmax", "max_logit", "masked", "tokens", "unmask"):
+        assert torch.equal(getattr(a, k), getattr(b, k)), k
