@@ -659,8 +659,7 @@ void launch_merge(const AttnParams& p, int total_block, int batch, hipStream_t s
 
 template <int D>
 __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParamsF32 p) {
-  attn_f32_role<D, kF32Threads>(p, blockIdx.x % p.tiles, blockIdx.x / p.tiles % p.hkv,
-                                blockIdx.x / p.tiles / p.hkv);
+  attn_f32_role<D, kF32Threads>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // attn_bf16_d128_kernel addresses a key row by a 32-bit byte offset from its segment's first
@@ -697,7 +696,9 @@ hipError_t block_attn(bool bf16, bool allow_split, const AttnArgs& a, void* ws, 
   const int max_keys = attn_max_keys(a);
   if (!bf16) {
     const AttnParamsF32 p = attn_params_f32(a);
-    const dim3 grid(static_cast<unsigned>(attn_f32_groups(a)));
+    // three dimensions: their product times the workgroup's threads may pass 2^32
+    const dim3 grid(static_cast<unsigned>(attn_f32_tiles(a)), static_cast<unsigned>(a.hkv),
+                    static_cast<unsigned>(a.batch));
     if (a.head_dim == 128)
       hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(kF32Threads), 0, s, p);
     else

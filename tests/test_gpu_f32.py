@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle
-from paper_2609_16450_amd import Ragged, eb_block_attn_dual, eb_lmhead_features
+from paper_2609_16450_amd import Ragged, eb_block_attn, eb_block_attn_dual, eb_lmhead_features
 
 pytestmark = pytest.mark.gpu
 
@@ -35,6 +35,23 @@ def test_attention_f32(blocks, prefix, suffix, group, head_dim):
                        *(torch.from_numpy(a).cuda() for a in kv), out)
     # scores of size |q||k| / sqrt(d) < 16 off by some 128 2^-24 16 / sqrt(128): 1e-5 in a weight
     np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
+
+
+def test_attention_f32_many_workgroups():
+    """A batch of one long block and thousands of single rows: 64 tiles x 32 heads x 4200 sequences
+    of 512 threads pass 2^32 threads.  A single row without a prefix attends to itself alone."""
+    lens = [1024] + [1] * 4199
+    print(f"attn f32 batch={len(lens)}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = (torch.randn(sum(lens), 32, 64, generator=g, device="cuda") for _ in range(3))
+    none = torch.empty(0, 32, 64, device="cuda")
+    out = torch.full(q.shape, 7.0, device="cuda")
+    eb_block_attn(Ragged.from_lengths(lens, [0] * len(lens)), q, k, v, none, none, out)
+    assert torch.equal(out[1024:], v[1024:])  # one weight of exactly one
+    x, y, z = (t[:1024].double().transpose(0, 1).contiguous() for t in (q, k, v))
+    ref = torch.softmax(x @ y.transpose(1, 2).contiguous() / 8.0, dim=-1) @ z
+    # scores of size |q||k| / sqrt(d) < 16 off by some 64 2^-24 16 / 8: 1e-5 in a weight
+    torch.testing.assert_close(out[:1024].double(), ref.transpose(0, 1), rtol=2e-5, atol=2e-5)
 
 
 # Slices of 64 and of 256 rows (70001 x 300 positions), odd and unaligned hidden sizes with and
