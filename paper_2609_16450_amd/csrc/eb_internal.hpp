@@ -69,7 +69,7 @@ hipError_t unmask_select_lps(int batch, const int32_t* cu_block, const float* co
                              const int32_t* argmax, const float* tau, const float* p_psi,
                              float tau_psi, uint8_t* masked, int32_t* tokens, uint8_t* unmask,
                              int32_t* n_commit, uint8_t* resolved, hipStream_t s);
-hipError_t unmask_select_topm(int batch, const int32_t* cu_block, const float* conf,
+hipError_t unmask_select_topm(int batch, int max_block, const int32_t* cu_block, const float* conf,
                               const int32_t* argmax, const float* tau, int m, uint8_t* masked,
                               int32_t* tokens, uint8_t* unmask, int32_t* n_commit,
                               uint8_t* resolved, hipStream_t s);

@@ -28,17 +28,17 @@ __global__ __launch_bounds__(kThreads) void unmask_kernel(
 // counts of a block of 256 rows are 65536 compares: 64 blocks of 16 to 256 rows take 9.1 us, where
 // one thread per row counting twice took 52 us.  Blocks of more than kRankTile rows are staged
 // tile by tile.
-constexpr int kTopmThreads = 1024;
-constexpr int kRankLanes = 4;                            // lanes that count one row's rank
-constexpr int kRankRows = kTopmThreads / kRankLanes;     // rows per round
-constexpr int kRankTile = 2048;                          // rows of a block staged at once
+constexpr int kRankLanes = 4;    // lanes that count one row's rank
+constexpr int kRankTile = 2048;  // rows of a block staged at once
 
+template <int kTopmThreads>  // 64, 256, 512 or 1024
 __global__ __launch_bounds__(kTopmThreads) void unmask_topm_kernel(
     const int32_t* __restrict__ cu_block, const float* __restrict__ conf,
     const int32_t* __restrict__ argmax, const float* __restrict__ tau, int budget,
     uint8_t* __restrict__ masked, int32_t* __restrict__ tokens, uint8_t* __restrict__ unmask,
     int32_t* __restrict__ n_commit, uint8_t* __restrict__ resolved) {
   constexpr int kWaves = kTopmThreads / 64;
+  constexpr int kRankRows = kTopmThreads / kRankLanes;  // rows per round
   __shared__ __attribute__((aligned(16))) float s_key[kRankTile];
   __shared__ int s_masked[kWaves], s_pass[kWaves];
   __shared__ Best s_best[kWaves];
@@ -202,13 +202,27 @@ hipError_t unmask_select_lps(int batch, const int32_t* cu_block, const float* co
   return hipGetLastError();
 }
 
-hipError_t unmask_select_topm(int batch, const int32_t* cu_block, const float* conf,
+hipError_t unmask_select_topm(int batch, int max_block, const int32_t* cu_block, const float* conf,
                               const int32_t* argmax, const float* tau, int m, uint8_t* masked,
                               int32_t* tokens, uint8_t* unmask, int32_t* n_commit,
                               uint8_t* resolved, hipStream_t s) {
-  hipLaunchKernelGGL(unmask_topm_kernel, dim3(batch), dim3(kTopmThreads), 0, s, cu_block, conf,
-                     argmax, tau, m, masked, tokens, unmask, n_commit, resolved);
-  return hipGetLastError();
+  if (m == 0)  // no row is within the budget: the threshold rule
+    return unmask_select(batch, max_block, cu_block, conf, argmax, tau, masked, tokens, unmask,
+                         n_commit, resolved, s);
+  // The fewest threads that rank a whole block in one round, up to 1024: a barrier costs less with
+  // fewer waves, and small workgroups share a compute unit.  With the copy that refills the mask
+  // flags, 32768 blocks of one row take 25 us with 64 threads, 290 us with 1024; 64 blocks of 16, 64
+  // and 128 rows 6.3, 7.4 and 8.5 us with one round of 64, 256 and 512 threads, 7.6, 8.4 and 9.1 us
+  // with 1024, and with two rounds 7.6 (32 rows by 64 threads) and 10.5 us (128 by 256).
+  auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(batch), dim3(threads), 0, s, cu_block, conf, argmax, tau, m,
+                       masked, tokens, unmask, n_commit, resolved);
+    return hipGetLastError();
+  };
+  if (max_block <= 64 / kRankLanes) return go(unmask_topm_kernel<64>, 64);
+  if (max_block <= 256 / kRankLanes) return go(unmask_topm_kernel<256>, 256);
+  if (max_block <= 512 / kRankLanes) return go(unmask_topm_kernel<512>, 512);
+  return go(unmask_topm_kernel<1024>, 1024);
 }
 
 hipError_t lps_features(int batch, const int32_t* cu_block, int vocab, const float* conf,

@@ -1,5 +1,6 @@
-"""Budgeted commit at the edges of its rounds (256 rows), LDS tiles (2048 rows) and remembered
-rounds (32), with ties in conf, against the oracle."""
+"""Budgeted commit at the edges of its workgroup sizes (blocks of up to 16, 64 and 128 rows), rounds
+(256 rows), LDS tiles (2048 rows) and remembered rounds (32), with ties in conf, against the
+oracle."""
 import numpy as np
 import pytest
 import torch
@@ -12,6 +13,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("m", [0, 1, 7, 300, 100000])
 @pytest.mark.parametrize("blocks", [
+    [1, 0, 16, 3], [0, 0], [17, 64, 1, 0], [65, 128, 4], [129, 127],
     [1, 0, 3, 64, 65, 255, 256, 257], [1023, 1024, 1025, 2047, 2048], [2049, 4100, 5], [8192, 9001]])
 def test_topm_edges(blocks, m):
     print(f"topm blocks={blocks} m={m}", flush=True)
