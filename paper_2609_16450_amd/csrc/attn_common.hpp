@@ -121,7 +121,11 @@ __device__ __forceinline__ void attn_merge_pair(const AttnParams& p, int rh, int
 #pragma unroll
   for (int j = 0; j < kGroup; ++j)
     if (j < nvalid) M = fmaxf(M, mk[j]);
-  for (int k = kGroup; k < nvalid; ++k) M = fmaxf(M, p.m_part[base + k]);
+  // the later groups' maxima, a lane each (fmaxf is exact, so the order does not matter)
+  if (nvalid > kGroup) {
+    for (int k = kGroup + lane; k < nvalid; k += 64) M = fmaxf(M, p.m_part[base + k]);
+    for (int mask = 32; mask >= 1; mask >>= 1) M = fmaxf(M, __shfl_xor(M, mask));
+  }
   float acc[kPer] = {};
   float L = 0.f;
   for (int k0 = 0; k0 < nvalid; k0 += kGroup) {
