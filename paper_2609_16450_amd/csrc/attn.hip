@@ -13,7 +13,6 @@
 // registers, V stored transposed in LDS).
 // Small steps (attn_small_ok) take the 16-row role of attn_small.hpp instead, here as a kernel
 // of its own; the decode step runs the same role inside the LM-head launch.
-#include <cstdlib>
 #include <cstring>
 
 #include "attn_common.hpp"
@@ -657,9 +656,80 @@ void launch_merge(const AttnParams& p, int total_block, int batch, hipStream_t s
     hipLaunchKernelGGL((attn_merge_kernel<D, 16>), grid, dim3(256), 0, s, p, total_block, batch);
 }
 
+template <int D, int kWaves>
+__global__ __launch_bounds__(kWaves * 64) void attn_f32_kernel(AttnParamsF32 p) {
+  attn_f32_role<D, kWaves * 64, kWaves>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+// fp32 attention of a handful of keys and query rows: one wavefront per (block row, query head), its
+// lanes over the head dimension, keys one by one with an online softmax.
 template <int D>
-__global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParamsF32 p) {
-  attn_f32_role<D, kF32Threads>(p, blockIdx.x, blockIdx.y, blockIdx.z);
+__global__ __launch_bounds__(64) void attn_f32_row_kernel(AttnParamsF32 p) {
+  constexpr int kPer = D / 64;
+  const int b = blockIdx.z, h = blockIdx.y, i = blockIdx.x, lane = threadIdx.x;
+  const int bbeg = p.cu_block[b];
+  const int len = p.cu_block[b + 1] - bbeg;
+  if (i >= len) return;  // whole workgroup
+  const int pbeg = p.cu_prefix[b];
+  const int plen = p.cu_prefix[b + 1] - pbeg;
+  const int sbeg = p.cu_suffix ? p.cu_suffix[b] : 0;
+  const int slen = p.cu_suffix ? p.cu_suffix[b + 1] - sbeg : 0;
+  const int g = h / p.group;
+  const size_t at = (static_cast<size_t>(bbeg + i) * p.hq + h) * D + lane;
+  float q[kPer], acc[kPer] = {};
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) q[e] = p.q[at + 64 * e];
+  float m = -INFINITY, l = 0.f;
+  auto walk = [&](int beg, int n, const float* __restrict__ k, const float* __restrict__ v) {
+    for (int j = 0; j < n; ++j) {
+      const size_t row = (static_cast<size_t>(beg + j) * p.hkv + g) * D + lane;
+      float dot = 0.f;
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) dot = fmaf(q[e], k[row + 64 * e], dot);
+      for (int mask = 32; mask >= 1; mask >>= 1) dot += __shfl_xor(dot, mask);
+      const float sc = dot * p.scale;
+      const float m_new = fmaxf(m, sc);
+      const float alpha = expf(m - m_new), w = expf(sc - m_new);
+      l = fmaf(l, alpha, w);
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) acc[e] = fmaf(acc[e], alpha, w * v[row + 64 * e]);
+      m = m_new;
+    }
+  };
+  walk(pbeg, plen, p.k_pre, p.v_pre);
+  walk(bbeg, len, p.k_blk, p.v_blk);
+  walk(sbeg, slen, p.k_suf, p.v_suf);
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) p.out[at + 64 * e] = acc[e] / l;
+}
+
+// Launch of the fp32 attention.
+//  * At most 8 (query row, key) pairs per sequence and K/V head: a wavefront per (row, head).  One
+//    row and 9 keys (head dimension 128): 31 us for 16384 of them against 43 us for MFMA tiles whose
+//    rows and keys are nearly all padding; 4 rows and 4 keys: 58 against 55 us.
+//  * At most 128 keys in 1024 or more tiles of query rows: one wave per tile.  There are waves
+//    enough, and eight per tile mostly wait for the merge: one row and 9, 58, 121 keys in 16384
+//    tiles 43, 188, 356 us against 204, 379, 509 us.
+//  * At most 64 keys: four waves, as the others have none (128 tiles of 16 keys: 6.1 against 7.0 us).
+//  * Else eight waves, which also keep few tiles busy.
+hipError_t launch_attn_f32(const AttnArgs& a, int max_keys, hipStream_t s) {
+  const AttnParamsF32 p = attn_params_f32(a);
+  // three dimensions: their product times the workgroup's threads may pass 2^32
+  auto go = [&](auto k64, auto k128, int waves, long x, int y) {
+    const dim3 grid(static_cast<unsigned>(x), static_cast<unsigned>(y),
+                    static_cast<unsigned>(a.batch));
+    hipLaunchKernelGGL(a.head_dim == 128 ? k128 : k64, grid, dim3(64 * waves), 0, s, p);
+    return hipGetLastError();
+  };
+  const long tiles = attn_f32_tiles(a);
+  if (attn_f32_few(a))
+    return go(attn_f32_row_kernel<64>, attn_f32_row_kernel<128>, 1, a.max_block, a.hq);
+  if (max_keys <= 128 && attn_f32_groups(a) >= 1024)
+    return go(attn_f32_kernel<64, 1>, attn_f32_kernel<128, 1>, 1, tiles, a.hkv);
+  if (max_keys <= 4 * kF32Keys)
+    return go(attn_f32_kernel<64, 4>, attn_f32_kernel<128, 4>, 4, tiles, a.hkv);
+  return go(attn_f32_kernel<64, kF32Waves>, attn_f32_kernel<128, kF32Waves>, kF32Waves, tiles,
+            a.hkv);
 }
 
 // attn_bf16_d128_kernel addresses a key row by a 32-bit byte offset from its segment's first
@@ -694,17 +764,7 @@ hipError_t block_attn(bool bf16, bool allow_split, const AttnArgs& a, void* ws, 
   if (a.total_block == 0 || a.max_block == 0) return hipSuccess;
   const int group = a.hq / a.hkv;
   const int max_keys = attn_max_keys(a);
-  if (!bf16) {
-    const AttnParamsF32 p = attn_params_f32(a);
-    // three dimensions: their product times the workgroup's threads may pass 2^32
-    const dim3 grid(static_cast<unsigned>(attn_f32_tiles(a)), static_cast<unsigned>(a.hkv),
-                    static_cast<unsigned>(a.batch));
-    if (a.head_dim == 128)
-      hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(kF32Threads), 0, s, p);
-    else
-      hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(kF32Threads), 0, s, p);
-    return hipGetLastError();
-  }
+  if (!bf16) return launch_attn_f32(a, max_keys, s);
   const SplitPlan sp = allow_split ? split_plan(a.batch, a.max_block, max_keys, a.hq, a.hkv)
                                    : SplitPlan{1, (max_keys + kKeys - 1) / kKeys * kKeys};
   const AttnParams p = attn_params(a, sp, ws);

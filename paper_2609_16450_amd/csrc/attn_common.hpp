@@ -62,10 +62,6 @@ inline SplitPlan split_plan(int batch, int max_block, int max_keys, int hq, int 
   return SplitPlan{nsplit, kps};
 }
 
-inline int attn_max_keys(const AttnArgs& a) {
-  return a.max_prefix + a.max_block + (a.cu_suffix ? a.max_suffix : 0);
-}
-
 // Parameters of a bf16 launch under plan sp; with a split the partials live in ws as
 // o [T * hq * nsplit, D], then m and l [T * hq * nsplit] each.
 inline AttnParams attn_params(const AttnArgs& a, const SplitPlan& sp, void* ws) {

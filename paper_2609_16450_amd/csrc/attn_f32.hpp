@@ -9,16 +9,15 @@ namespace {
 
 // fp32 attention, as the role of a workgroup: a kernel of its own (attn_f32_kernel) or, in a small
 // step, the last workgroups of the epilogue launch, which saves the step a launch.  One workgroup of
-// eight wavefronts per (sequence, K/V head, 16 query rows), where the query rows are the (position,
-// head-in-group) pairs.  Wave v takes the 16-key chunks v, v + 8,
-// ... of the sequence's keys with an online softmax of its own, and the eight partial results are
-// merged through LDS.  Scores are formed transposed, S^T = K Q^T, by 16x16x4 fp32 MFMAs (fp32
-// multiply-adds): lane l owns query l % 16 and holds keys 4 (l / 16) + r of the chunk, which are
-// exactly the k-slots of the B operand of O^T = V^T P^T, one register r per MFMA.  Contraction
-// indices are permuted so that K and Q arrive by 16-byte loads; K and V come straight from global
-// memory (each element is used once per workgroup).  Bound by latency at the sizes this path
-// serves: 32 rows x 4 heads x 64 over 128 keys take 6.3 us, where a wavefront per (row, head)
-// that walked the keys one by one took 61 us.
+// kWaves wavefronts per (sequence, K/V head, 16 query rows), where the query rows are the (position,
+// head-in-group) pairs.  Wave v takes the 16-key chunks v, v + kWaves, ... of the sequence's keys
+// with an online softmax of its own, and the waves' partial results are merged through LDS.  Scores
+// are formed transposed, S^T = K Q^T, by 16x16x4 fp32 MFMAs (fp32 multiply-adds): lane l owns query
+// l % 16 and holds keys 4 (l / 16) + r of the chunk, which are exactly the k-slots of the B operand
+// of O^T = V^T P^T, one register r per MFMA.  Contraction indices are permuted so that K and Q
+// arrive by 16-byte loads; K and V come straight from global memory (each element is used once per
+// workgroup).  Bound by latency at the sizes this path serves: 32 rows x 4 heads x 64 over 128 keys
+// take 6.3 us, where a wavefront per (row, head) that walked the keys one by one took 61 us.
 struct AttnParamsF32 {
   const int32_t* cu_block;
   const int32_t* cu_prefix;
@@ -35,11 +34,9 @@ struct AttnParamsF32 {
   const float* v_suf;
 };
 
-constexpr int kF32Waves = 8;
+constexpr int kF32Waves = 8;  // waves over the keys in a small step, and of launch_attn_f32
 constexpr int kF32Rows = 16;  // query rows per workgroup
 constexpr int kF32Keys = 16;  // keys per chunk
-
-constexpr int kF32Threads = kF32Waves * 64;
 
 // Workgroups of the role, one per (tile of query rows, K/V head, sequence), and its parameters.
 inline long attn_f32_tiles(const AttnArgs& a) {
@@ -48,20 +45,26 @@ inline long attn_f32_tiles(const AttnArgs& a) {
 inline long attn_f32_groups(const AttnArgs& a) { return attn_f32_tiles(a) * a.hkv * a.batch; }
 inline AttnParamsF32 attn_params_f32(const AttnArgs& a) {
   auto f = [](const void* x) { return static_cast<const float*>(x); };
+// Too few rows and keys for MFMA tiles (see launch_attn_f32).
+inline bool attn_f32_few(const AttnArgs& a) {
+  return static_cast<long>(a.max_block) * (a.hq / a.hkv) * attn_max_keys(a) <= 8;
+}
   return AttnParamsF32{a.cu_block, a.cu_prefix, a.hq, a.hkv, a.hq / a.hkv,
                        static_cast<int>(attn_f32_tiles(a)), a.scale, f(a.q), f(a.k_blk),
                        f(a.v_blk), f(a.k_pre), f(a.v_pre), static_cast<float*>(a.out),
                        a.cu_suffix, f(a.k_suf), f(a.v_suf)};
 }
 
-// Role of the workgroup of tile `tile`, K/V head g and sequence b.  Every thread of the workgroup calls it; waves past kF32Waves only help
-// with the final merge, so the results do not depend on the workgroup's size.
-template <int D, int kThreads>
+// Role of the workgroup of tile `tile`, K/V head g and sequence b.  Every thread of the workgroup
+// calls it; waves past kWaves only help with the final merge, so the results do not depend on the
+// workgroup's size.  Nor do they depend on kWaves as long as no wave has a second chunk: a wave
+// without keys adds exact zeros.
+template <int D, int kThreads, int kWaves>
 __device__ __forceinline__ void attn_f32_role(const AttnParamsF32& p, int tile, int g, int b) {
   constexpr int kChunks = D / 16;  // 16-column chunks of the head dimension
   constexpr int kPitch = D + 4;    // LDS row pitch of a partial O
-  __shared__ __attribute__((aligned(16))) float s_o[kF32Waves][kF32Rows * kPitch];
-  __shared__ float s_m[kF32Waves][kF32Rows], s_l[kF32Waves][kF32Rows];
+  __shared__ __attribute__((aligned(16))) float s_o[kWaves][kF32Rows * kPitch];
+  __shared__ float s_m[kWaves][kF32Rows], s_l[kWaves][kF32Rows];
   const int row0 = tile * kF32Rows;
   const int bbeg = p.cu_block[b];
   const int len = p.cu_block[b + 1] - bbeg;
@@ -89,7 +92,7 @@ __device__ __forceinline__ void attn_f32_role(const AttnParamsF32& p, int tile, 
   };
 
   // MFMA e of chunk c contracts over d = 16 c + 4 (l / 16) + e.
-  if (wave < kF32Waves) {
+  if (wave < kWaves) {
     f32x4u qf[kChunks];
     const float* q = p.q + row_off(l16) + 4 * grp;
 #pragma unroll
@@ -156,10 +159,10 @@ __device__ __forceinline__ void attn_f32_role(const AttnParamsF32& p, int tile, 
     if (row0 + r >= n_rows) break;
     float m = s_m[0][r];
 #pragma unroll
-    for (int v = 1; v < kF32Waves; ++v) m = fmaxf(m, s_m[v][r]);
+    for (int v = 1; v < kWaves; ++v) m = fmaxf(m, s_m[v][r]);
     float l = 0.f, x = 0.f;
 #pragma unroll
-    for (int v = 0; v < kF32Waves; ++v) {
+    for (int v = 0; v < kWaves; ++v) {
       const float f = expf(s_m[v][r] - m);
       l = fmaf(f, s_l[v][r], l);
       x = fmaf(f, s_o[v][r * kPitch + d], x);

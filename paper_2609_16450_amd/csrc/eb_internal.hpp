@@ -36,6 +36,9 @@ struct AttnArgs {
   const void* k_suf = nullptr;
   const void* v_suf = nullptr;
 };
+inline int attn_max_keys(const AttnArgs& a) {
+  return a.max_prefix + a.max_block + (a.cu_suffix ? a.max_suffix : 0);
+}
 // Workspace for key-split partials (0 when the launch needs no split).  Without allow_split
 // one workgroup covers all keys of its query tile and no workspace is used.  max_keys is the
 // largest number of keys of a sequence (prefix + block + suffix).

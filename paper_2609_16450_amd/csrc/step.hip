@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kFinishThreads) void step_finish_kernel(
   if constexpr (kF32) {
     if (b >= batch) {  // whole workgroup
       const int tile = (b - batch) % ap32.tiles, gb = (b - batch) / ap32.tiles;
-      attn_f32_role<D, kFinishThreads>(ap32, tile, gb % ap32.hkv, gb / ap32.hkv);
+      attn_f32_role<D, kFinishThreads, kF32Waves>(ap32, tile, gb % ap32.hkv, gb / ap32.hkv);
       return;
     }
   }
@@ -122,7 +122,7 @@ bool step_finish_fusable(int max_block, int n_slices) {
 // attention kernel's own: 512 to 2048 workgroups took 45 against 42 us, 270 against 190 us and 1239
 // against 793 us (head dimension 128), at 64 up to a fifth more.
 bool step_finish_hosts_attn(bool bf16, const AttnArgs& a) {
-  return !bf16 && a.total_block > 0 && attn_f32_groups(a) <= 256;
+  return !bf16 && a.total_block > 0 && attn_f32_groups(a) <= 256 && !attn_f32_few(a);
 }
 
 hipError_t step_finish(bool bf16, bool attn_f32, const AttnArgs& a, void* attn_ws, int n_rows, int vocab,

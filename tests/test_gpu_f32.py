@@ -37,6 +37,36 @@ def test_attention_f32(blocks, prefix, suffix, group, head_dim):
     np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
 
 
+def _attention(blocks, prefix, x, group):
+    """Output of eb_block_attn and the oracle's; x: q, k_blk, v_blk, k_pre, v_pre."""
+    out = torch.full(x[0].shape, 7.0, device="cuda")
+    eb_block_attn(Ragged.from_lengths(blocks, prefix), *(torch.from_numpy(a).cuda() for a in x), out)
+    hkv = x[1].shape[1]
+    with np.errstate(all="ignore"):
+        return out.cpu().numpy(), oracle.block_attention(*x, _cu(blocks), _cu(prefix), hkv * group,
+                                                         hkv)
+
+
+# Both sides of the launch rules: 8 and 9 (row, key) pairs; 64 and 65 keys; 1022 and 1024 tiles of
+# query rows with 128 and 129 keys.  Every fourth sequence is shorter than the largest.
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("batch,rows,keys,group", [
+    (3, 1, 8, 1), (3, 1, 9, 1), (2, 2, 4, 1), (5, 1, 2, 4), (5, 1, 2, 5),
+    (4, 3, 64, 2), (4, 3, 65, 2), (511, 1, 20, 1), (512, 1, 20, 1), (512, 2, 128, 3),
+    (512, 2, 129, 3)])
+def test_attention_f32_launches(batch, rows, keys, group, head_dim):
+    print(f"attn f32 batch={batch} rows={rows} keys={keys} G={group} D={head_dim}", flush=True)
+    blocks = [rows] * batch
+    prefix = [(keys - rows) // (4 if b % 4 == 3 else 1) for b in range(batch)]
+    rng = np.random.default_rng([batch, rows, keys, head_dim])
+    T, S = sum(blocks), sum(prefix)
+    x = [rng.standard_normal((n, hh, head_dim), dtype=np.float32)
+         for n, hh in ((T, 2 * group), (T, 2), (T, 2), (S, 2), (S, 2))]
+    got, ref = _attention(blocks, prefix, x, group)
+    # scores of size |q||k| / sqrt(d) < 16 off by some 128 2^-24 16 / sqrt(128): 1e-5 in a weight
+    np.testing.assert_allclose(got, ref, rtol=2e-5, atol=2e-5)
+
+
 def test_attention_f32_many_workgroups():
     """A batch of one long block and thousands of single rows: 64 tiles x 32 heads x 4200 sequences
     of 512 threads pass 2^32 threads.  A single row without a prefix attends to itself alone."""

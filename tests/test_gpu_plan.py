@@ -56,12 +56,13 @@ def test_epilogue_rule(rows, vocab):
 # fp32 steps, bit for bit against the separate entry points.  The attention is in the epilogue launch
 # with up to 256 workgroups (tiles of 16 query rows, K/V heads, sequences), when that is one launch:
 # 70001 entries are 274 slices, so a block of 29 rows has 7946 partials (one launch) and one of 30
-# rows 8220 (three kernels).  Empty blocks, and both head dimensions in the epilogue.
+# rows 8220 (three kernels).  Empty blocks, both head dimensions in the epilogue, and a step of four
+# (row, key) pairs, whose attention is a launch of its own.
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("lens,hq,hkv,vocab", [
     ((20, 0, 7, 33), 4, 2, 2048), ((0, 1, 5, 0), 3, 1, 300),
     ((16,) * 8, 32, 32, 999), ((16,) * 8 + (1,), 32, 32, 999),  # 256 workgroups, 288
-    ((29, 3), 2, 2, 70001), ((30, 3), 2, 2, 70001)])
+    ((29, 3), 2, 2, 70001), ((30, 3), 2, 2, 70001), ((2,), 2, 2, 300)])
 def test_fp32_step(lens, hq, hkv, vocab, head_dim):
     print(f"fp32 step blocks={lens} hq={hq} hkv={hkv} V={vocab} D={head_dim}", flush=True)
     T, B, hidden = sum(lens), len(lens), 100
