@@ -1,6 +1,8 @@
 // Block attention in fp32, shared by the attention kernel and the fp32 step.
 #pragma once
 
+#include <cfloat>
+
 #include "eb_common.hpp"
 #include "eb_internal.hpp"
 
@@ -43,12 +45,12 @@ inline long attn_f32_tiles(const AttnArgs& a) {
   return (static_cast<long>(a.max_block) * (a.hq / a.hkv) + kF32Rows - 1) / kF32Rows;
 }
 inline long attn_f32_groups(const AttnArgs& a) { return attn_f32_tiles(a) * a.hkv * a.batch; }
-inline AttnParamsF32 attn_params_f32(const AttnArgs& a) {
-  auto f = [](const void* x) { return static_cast<const float*>(x); };
 // Too few rows and keys for MFMA tiles (see launch_attn_f32).
 inline bool attn_f32_few(const AttnArgs& a) {
   return static_cast<long>(a.max_block) * (a.hq / a.hkv) * attn_max_keys(a) <= 8;
 }
+inline AttnParamsF32 attn_params_f32(const AttnArgs& a) {
+  auto f = [](const void* x) { return static_cast<const float*>(x); };
   return AttnParamsF32{a.cu_block, a.cu_prefix, a.hq, a.hkv, a.hq / a.hkv,
                        static_cast<int>(attn_f32_tiles(a)), a.scale, f(a.q), f(a.k_blk),
                        f(a.v_blk), f(a.k_pre), f(a.v_pre), static_cast<float*>(a.out),
@@ -100,8 +102,9 @@ __device__ __forceinline__ void attn_f32_role(const AttnParamsF32& p, int tile, 
     f32x4 o[kChunks];
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) o[c] = f32x4{};
-    float m_run = -INFINITY, l_run = 0.f;
-    for (int k0 = wave * kF32Keys; k0 < n_keys; k0 += kF32Waves * kF32Keys) {
+    // from the lowest finite value on: a chunk whose scores are all -inf then has weights of zero
+    float m_run = -FLT_MAX, l_run = 0.f;
+    for (int k0 = wave * kF32Keys; k0 < n_keys; k0 += kWaves * kF32Keys) {
       // keys past the end are loaded from the last, valid one; their scores are set to -inf
       const float* kp = key_src(min(k0 + l16, n_keys - 1), p.k_pre, p.k_blk, p.k_suf) + 4 * grp;
       f32x4u kf[kChunks];
@@ -113,6 +116,13 @@ __device__ __forceinline__ void attn_f32_role(const AttnParamsF32& p, int tile, 
         const float* vp = key_src(min(k0 + 4 * grp + r, n_keys - 1), p.v_pre, p.v_blk, p.v_suf);
 #pragma unroll
         for (int c = 0; c < kChunks; ++c) vf[r][c] = vp[16 * c + l16];
+      }
+      if (k0 + kF32Keys > n_keys) {  // no V past the end: its weight of zero times infinity is NaN
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int c = 0; c < kChunks; ++c)
+            vf[r][c] = k0 + 4 * grp + r < n_keys ? vf[r][c] : 0.f;
       }
       f32x4 acc[2] = {f32x4{}, f32x4{}};
 #pragma unroll
@@ -127,7 +137,7 @@ __device__ __forceinline__ void attn_f32_role(const AttnParamsF32& p, int tile, 
       }
       mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
       mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-      const float m_new = fmaxf(m_run, mloc);  // finite: the chunk has a valid key
+      const float m_new = fmaxf(m_run, mloc);
       const float alpha = expf(m_run - m_new);
       m_run = m_new;
       l_run *= alpha;
@@ -153,7 +163,7 @@ __device__ __forceinline__ void attn_f32_role(const AttnParamsF32& p, int tile, 
       *reinterpret_cast<f32x4*>(&s_o[wave][l16 * kPitch + 16 * c + 4 * grp]) = o[c];
   }
   __syncthreads();
-  // merge in wave order; a wave without keys has m = -inf and weight 0
+  // merge in wave order; a wave without keys has l = 0 and o = 0
   for (int i = tid; i < kF32Rows * D; i += kThreads) {
     const int r = i / D, d = i % D;
     if (row0 + r >= n_rows) break;

@@ -67,6 +67,22 @@ def test_attention_f32_launches(batch, rows, keys, group, head_dim):
     np.testing.assert_allclose(got, ref, rtol=2e-5, atol=2e-5)
 
 
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_attention_f32_infinities(head_dim):
+    """Scores of -inf have a weight of zero, and an infinite value of the last key, which the tile's
+    keys past the end repeat, reaches the output."""
+    rng = np.random.default_rng(head_dim)
+    x = [rng.standard_normal((n, 1, head_dim), dtype=np.float32) for n in (5, 5, 5, 48, 48)]
+    q, k_blk, v_blk, k_pre, v_pre = x
+    q[:, 0, 0], k_blk[:, 0, 0], k_pre[:, 0, 0] = 3e20, 0, 0
+    k_pre[16:32, 0, 0] = -3e20          # a whole chunk of keys
+    v_blk[4, 0, 7] = np.inf
+    got, ref = _attention([5], [48], x, 1)
+    assert np.isinf(got[:, 0, 7]).all()
+    got[:, 0, 7] = ref[:, 0, 7] = 0
+    np.testing.assert_allclose(got, ref, rtol=2e-5, atol=2e-5)
+
+
 def test_attention_f32_many_workgroups():
     """A batch of one long block and thousands of single rows: 64 tiles x 32 heads x 4200 sequences
     of 512 threads pass 2^32 threads.  A single row without a prefix attends to itself alone."""
