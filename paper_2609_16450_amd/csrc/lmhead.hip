@@ -76,8 +76,9 @@ __device__ __forceinline__ float top2_shfl_merge(float m, float m2, int mask) {
 // Statistics of column l % 16 of position tile nt of a wave's natural-order 16x16 accumulator
 // tiles, whose rows are vocabulary entries wb + 16 tm + 4 (l / 16) + r below we: per lane, then
 // merged over the column's four lanes in a canonical order.  With kTop2, m2 is the second-largest
-// logit (kNegBig if none).
-template <int TM, int NT, bool kTop2>
+// logit (kNegBig if none).  With kAnyLogit, logits of -inf (and NaN) add nothing, instead of the NaN
+// that 0 * -inf makes of t; no other result changes.
+template <int TM, int NT, bool kTop2, bool kAnyLogit = false>
 __device__ __forceinline__ Partial wave_column_stats(const f32x4 (&acc)[TM][NT], int nt, int wb,
                                                      int we, int lane, float& m2) {
   const int grp = lane >> 4;
@@ -103,7 +104,8 @@ __device__ __forceinline__ Partial wave_column_stats(const f32x4 (&acc)[TM][NT],
     for (int r = 0; r < 4; ++r) {
       const int v = wb + tm * 16 + 4 * grp + r;
       if (v < we) {
-        const float y = (acc[tm][nt][r] - m) * kLog2e;
+        float y = (acc[tm][nt][r] - m) * kLog2e;
+        if (kAnyLogit) y = fmaxf(y, -1.0e30f);
         const float e = fast_exp2(y);
         s += e;
         t = fmaf(e, y, t);
@@ -992,7 +994,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void lmhead_f32_kernel(
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     float m2 = kNegBig;
-    const Partial p = wave_column_stats<TM, NT, kTop2>(acc, nt, wb, we, lane, m2);
+    const Partial p = wave_column_stats<TM, NT, kTop2, true>(acc, nt, wb, we, lane, m2);
     if (lane < 16) {
       red[wave][nt * 16 + l16] = p;
       if (kTop2) red2[wave][nt * 16 + l16] = m2;

@@ -4,7 +4,8 @@ import pytest
 import torch
 
 import oracle
-from paper_2609_16450_amd import Ragged, eb_block_attn, eb_block_attn_dual, eb_lmhead_features
+from paper_2609_16450_amd import (Ragged, eb_block_attn, eb_block_attn_dual, eb_lmhead_confidence,
+                                  eb_lmhead_features)
 
 pytestmark = pytest.mark.gpu
 
@@ -81,6 +82,31 @@ def test_attention_f32_infinities(head_dim):
     assert np.isinf(got[:, 0, 7]).all()
     got[:, 0, 7] = ref[:, 0, 7] = 0
     np.testing.assert_allclose(got, ref, rtol=2e-5, atol=2e-5)
+
+
+@pytest.mark.parametrize("rows,vocab", [(3, 300), (300, 70001)])  # slices of 64 and of 256 rows
+def test_lmhead_f32_infinities(rows, vocab):
+    """Logits of -inf, of the lowest finite value and NaN take no part in the statistics."""
+    rng = np.random.default_rng([rows, vocab])
+    h, w = (rng.standard_normal((n, 65), dtype=np.float32) for n in (rows, vocab))
+    h[:, 3] = 1
+    bad = rng.permutation(vocab)[:120]
+    w[bad] = 0
+    w[bad[:40], 3], w[bad[40:80], 3] = -np.inf, np.finfo(np.float32).min
+    w[bad[80:], 3] = np.nan
+    good = np.setdiff1d(np.arange(vocab), bad)
+    z = h.astype(np.float64) @ w[good].astype(np.float64).T
+    p = np.exp(z - z.max(axis=1, keepdims=True))
+    p /= p.sum(axis=1, keepdims=True)
+    conf, ent, top = (torch.empty(rows, device="cuda") for _ in range(3))
+    arg = torch.empty(rows, dtype=torch.int32, device="cuda")
+    eb_lmhead_confidence(torch.from_numpy(h).cuda(), torch.from_numpy(w).cuda(), conf, ent, arg, top)
+    np.testing.assert_array_equal(arg.cpu().numpy(), good[z.argmax(axis=1)])
+    # logits of size 65 off by some 65 2^-24 of that: 3e-4 at most, relative in conf
+    np.testing.assert_allclose(conf.cpu().numpy(), p.max(axis=1), rtol=1e-3)
+    np.testing.assert_allclose(ent.cpu().numpy(), -(p * np.log(np.maximum(p, 1e-300))).sum(axis=1),
+                               rtol=1e-3, atol=1e-3)
+    np.testing.assert_allclose(top.cpu().numpy(), z.max(axis=1), rtol=1e-5)
 
 
 def test_attention_f32_many_workgroups():
