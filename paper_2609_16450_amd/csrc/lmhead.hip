@@ -19,17 +19,18 @@ namespace eb {
 namespace {
 
 // ---------------------------------------------------------------------------------------
-// Streaming kernel for few block positions (n_rows <= 32 * NT).
+// Streaming kernel for few block positions (n_rows <= 16 * NT).
 //
 // With a handful of positions the product is a bandwidth-bound pass over W.  One workgroup per
 // compute unit owns a contiguous slice of vocabulary rows.  Each of its 16 waves (8 for slices
 // above 768 rows) streams its share of the slice from HBM straight into MFMA A-operand
 // registers, keeping kDepth k-steps of loads in flight; h, the B operand shared by all waves,
 // goes through a double-buffered LDS chunk.  Every W byte is read once, by one lane, with no
-// LDS round trip, in whole cache lines (line_to_frag).  Bound by HBM: 32 positions of a 126464 x
-// 4096 head take 173 us (6.0 TB/s) with whole lines against 177.5 us with half lines on one
-// machine, 64 positions 177.6 against 185 us; of a 152064 x 3584 head 185.5 against 200 us and
-// 197.6 against 214 us.  (Loading h per wave straight into registers instead, with no LDS and no
+// LDS round trip, in whole or half cache lines per load (kLines).  Bound by HBM: 32 positions of a
+// 126464 x 4096 head take 178 us (5.8 TB/s) where W lies well in memory, against 184 us with half
+// lines and 32-column steps, 64 positions 181 against 188 us (195 to 222 against 202 to 228 us at
+// other allocations); of a 152064 x 3584 head 187 against 202 us and 199 against 215 us.
+// (Loading h per wave straight into registers instead, with no LDS and no
 // barrier, measured 237 us against 203 us at 32 positions: the per-wave h traffic from L2 costs
 // more than the shared chunks.)
 // ---------------------------------------------------------------------------------------
@@ -39,14 +40,16 @@ namespace {
 constexpr int kStreamGroups = EB_STREAM_GROUPS;  // workgroups (256: one per compute unit)
 
 // The streaming kernel uses 16x16x32 MFMA tiles (mfma16; 32x32x16 tiles measured 4.65 TB/s at best
-// against 5.4).  A lane of the A operand holds 8 k-values of row l % 16, so loads straight into
-// that layout would read 16 rows x 64 bytes, half a cache line per row.  Instead a k-step is 64
-// columns of a 16-row tile in two loads of 8 rows x 128 bytes: lane l loads 16-byte chunk
-// line_chunk(l) of row l % 8 (v0) and of row 8 + l % 8 (v1).  line_to_frag exchanges v0 and v1
-// between lanes l and l ^ 8, after which lane l holds row l % 16 in both, chunk l / 16 in the first
-// and 4 + l / 16 in the second: the A operands of the MFMAs of the step's first and last 32 columns.
-// A logit is thus summed in the order of its columns, as in the tile kernel, so a position's logits
-// do not depend on how many positions the call has.
+// against 5.4).  A lane of the A operand holds 8 k-values of row l % 16.
+//  * Half lines: a k-step is 32 columns, loaded straight into that layout, 16 rows x 64 bytes per
+//    load.
+//  * Whole lines (kLines): a k-step is 64 columns of a 16-row tile in two loads of 8 rows x 128
+//    bytes: lane l loads 16-byte chunk line_chunk(l) of row l % 8 (v0) and of row 8 + l % 8 (v1).
+//    line_to_frag exchanges v0 and v1 between lanes l and l ^ 8, after which lane l holds row l % 16
+//    in both, chunk l / 16 in the first and 4 + l / 16 in the second: the A operands of the MFMAs of
+//    the step's first and last 32 columns.
+// Either way a logit is summed in the order of its columns, as in the tile kernel, so a position's
+// logits do not depend on how many positions the call has.
 __device__ __forceinline__ int line_chunk(int lane) { return (lane >> 4) + 4 * ((lane >> 3) & 1); }
 __device__ __forceinline__ void line_to_frag(const u32x4& v0, const u32x4& v1, bf16x8& first,
                                              bf16x8& last) {
@@ -119,10 +122,11 @@ __device__ __forceinline__ Partial wave_column_stats(const f32x4 (&acc)[TM][NT],
 }
 
 // kTop2: also track the second-largest logit of each (row, slice) into part2.
-// kWaves waves per workgroup, NL 8-row loads (half MFMA tiles) per wave, NT 16-position tiles.
+// kWaves waves per workgroup, shares of at most 8 NL vocabulary rows per wave (NL whole-line loads
+// per k-step), NT 16-position tiles.
 // kAttnD != 0: workgroups n_slices and up run the small block attention (head dimension kAttnD)
 // on unit blockIdx.x - n_slices of ap; the dispatcher starts them as the slices finish.
-template <int kWaves, int NL, int NT, int kDepth, bool kTop2, int kAttnD>
+template <int kWaves, int NL, int NT, int kDepth, bool kTop2, int kAttnD, bool kLines>
 __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
     const uint16_t* __restrict__ h, const uint16_t* __restrict__ w, int n_rows, int hidden,
     int vocab, int rows_per_wg, Partial* __restrict__ part, float* __restrict__ part2,
@@ -135,9 +139,11 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
     }
   }
   constexpr int TM = (NL + 1) / 2;     // 16-row tiles; the last one may lack its upper rows
+  constexpr int kCols = kLines ? 64 : 32;   // columns per k-step
+  constexpr int kLoads = kLines ? NL : TM;  // loads per k-step
   constexpr int KC = 1024 / NT;        // h columns per LDS chunk
   constexpr int kPitch = KC + 8;       // LDS row pitch (bf16)
-  constexpr int kSpc = KC / 64;        // k-steps per chunk
+  constexpr int kSpc = KC / kCols;     // k-steps per chunk
   constexpr int kHRows = NT * 16;
   constexpr int kHChunks16 = kHRows * KC / 8;
   constexpr int kThreads = kWaves * 64;
@@ -155,15 +161,16 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
   const int wb = vb + wave * rw;
   const int we = min(ve, wb + rw);
 
-  // Unconditional loads with clamped addresses: rows 8 i + l % 8 of the wave's share.
+  // Unconditional loads with clamped addresses: rows 8 i + l % 8 of the wave's share, or 16 i +
+  // l % 16.
   const int wlast = max(min(we, vocab) - 1, 0);
-  const uint16_t* wp[NL];
+  const uint16_t* wp[kLoads];
 #pragma unroll
-  for (int i = 0; i < NL; ++i) {
-    const int row = min(wb + i * 8 + (lane & 7), wlast);
-    wp[i] = w + static_cast<size_t>(row) * hidden + 8 * line_chunk(lane);
+  for (int i = 0; i < kLoads; ++i) {
+    const int row = min(wb + (kLines ? i * 8 + (lane & 7) : i * 16 + l16), wlast);
+    wp[i] = w + static_cast<size_t>(row) * hidden + 8 * (kLines ? line_chunk(lane) : grp);
   }
-  const int nsteps = hidden / 64;
+  const int nsteps = hidden / kCols;
   const int nsteps_p = (nsteps + kDepth - 1) / kDepth * kDepth;
   const int nchunks = (hidden + KC - 1) / KC;
 
@@ -171,11 +178,12 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
   // worst of nine allocations of W, at 32 positions or one, took 188 us instead of 205-233 us, but
   // a logit's sum then depended on its vocabulary slice: equal rows of W got unequal logits, and
   // neither the lowest id nor a gap of 0 on a shared maximum held any more.)
-  u32x4 buf[kDepth][NL];
+  u32x4 buf[kDepth][kLoads];
   auto issue = [&](int j, int step) {
     const int st = min(step, nsteps - 1);
 #pragma unroll
-    for (int i = 0; i < NL; ++i) buf[j][i] = *reinterpret_cast<const u32x4*>(wp[i] + 64 * st);
+    for (int i = 0; i < kLoads; ++i)
+      buf[j][i] = *reinterpret_cast<const u32x4*>(wp[i] + kCols * st);
   };
   u32x4 hreg[kHPer];
   auto load_h = [&](int c) {
@@ -211,19 +219,38 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
   if (nchunks > 1) load_h(1);
 
   auto consume = [&](int g, int j) {
-    const uint16_t* hb = hs[(g / kSpc) & 1] + (g % kSpc) * 64 + 8 * grp + 64 * j;
-    bf16x8 a[TM][2];
+    constexpr int kMfmas = kCols / 32;  // MFMAs per tile and k-step
+    const uint16_t* hb = hs[(g / kSpc) & 1] + (g % kSpc) * kCols + 8 * grp + kCols * j;
+    bf16x8 a[TM][kMfmas];
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm)  // (upper rows that are not there repeat the lower ones)
-      line_to_frag(buf[j][2 * tm], buf[j][min(2 * tm + 1, NL - 1)], a[tm][0], a[tm][1]);
+    for (int tm = 0; tm < TM; ++tm) {  // (upper rows that are not there repeat the lower ones)
+      if constexpr (kLines)
+        line_to_frag(buf[j][2 * tm], buf[j][min(2 * tm + 1, NL - 1)], a[tm][0], a[tm][1]);
+      else
+        a[tm][0] = __builtin_bit_cast(bf16x8, buf[j][tm]);
+    }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < kMfmas; ++i) {
+      auto frag = [&](int nt) {
+        return *reinterpret_cast<const bf16x8*>(hb + (nt * 16 + l16) * kPitch + 32 * i);
+      };
+      if constexpr (kLines) {  // (all NT fragments together spill: 1 to 3% at 152064 x 3584)
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(hb + (nt * 16 + l16) * kPitch + 32 * i);
+        for (int nt = 0; nt < NT; ++nt) {
+          const bf16x8 b = frag(nt);
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) acc[tm][nt] = mfma16(a[tm][i], b, acc[tm][nt]);
+          for (int tm = 0; tm < TM; ++tm) acc[tm][nt] = mfma16(a[tm][i], b, acc[tm][nt]);
+        }
+      } else {
+        bf16x8 b[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) b[nt] = frag(nt);
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) acc[tm][nt] = mfma16(a[tm][i], b[nt], acc[tm][nt]);
       }
+    }
   };
   auto chunk_boundary = [&](int g) {
     if (g > 0 && g % kSpc == 0) {
@@ -274,14 +301,8 @@ __global__ __launch_bounds__(kWaves * 64) void lmhead_stream16_kernel(
   }
 }
 
-// k-steps of W loads in flight per wave with 16 waves (measured on MI355X; the macro exists so
-// that other settings can be built and timed).
-#ifndef EB_STREAM_DEPTH
-#define EB_STREAM_DEPTH 4
-#endif
 constexpr int kStreamShape = 16;  // rows (and positions) per MFMA tile
 constexpr int kStreamLoad = 8;    // rows per load
-constexpr int kStreamDepth = EB_STREAM_DEPTH;
 // 16 waves per workgroup while each wave's share of the slice fits in kStreamMaxTm16 row tiles
 // (at 1024 threads a lane has 128 VGPRs; four tiles with two or more position tiles spill), else
 // 8 waves, which leaves 256 VGPRs per lane for up to 8 row tiles (16 waves with depth 8 measured
@@ -321,22 +342,53 @@ struct HostedAttn {
   int units, attn_d;
 };
 
-template <int kWaves, int NL, int NT, bool kTop2, int kAttnD = 0>
-hipError_t launch_stream_nl(int n_rows, int hidden, int vocab, const StreamPlan& pl,
-                            const void* h, const void* w, Partial* part, float* part2,
-                            hipStream_t s, const HostedAttn& ha) {
+// Whole lines or half lines per load.  Half lines make the shorter k-step, so the loop runs closer
+// to its loads; whole lines make half the requests.  With three or more 8-row shares per wave what
+// decides is whether W fits the 256 MB cache in front of HBM, where a program that calls the head
+// again and again finds it: whole lines take 2 to 5% longer up to 260 MB (100000 x 1024: 37.3 -> 38.9
+// us for one position, 41.2 -> 43.0 us for 64) and 2 to 8% less above 300 MB (126464 x 4096: 193.7 ->
+// 183.1 us, 195.4 -> 189.0 us).  With two, half lines are never behind (65536 x 2048: 42.8 against
+// 48.6 us for one position; x 4096: 110.7 against 112.9 us).  With one, whole lines read 8 rows
+// instead of 16 (8192 x 2048: 16.5 -> 13.9 us), except that with four position tiles there is nothing
+// to gain (24000 x 4096, 64 positions: 45.4 -> 48.7 us).
+constexpr size_t kStreamLineBytes = 280u << 20;
+enum StreamForm { kHalfLines, kWholeLines, kBySize };
+template <int kWaves, int NL, int NT>
+constexpr StreamForm kStreamForm = kWaves == 8 || (NL == 1 && NT <= 2) ? kWholeLines
+                                   : NL <= 2                           ? kHalfLines
+                                                                       : kBySize;
+
+template <int kWaves, int NL, int NT, bool kTop2, int kAttnD, bool kLines>
+hipError_t launch_stream_form(int n_rows, int hidden, int vocab, const StreamPlan& pl,
+                              const void* h, const void* w, Partial* part, float* part2,
+                              hipStream_t s, const HostedAttn& ha) {
   // 16 waves: up to 16 W registers in flight per lane (16 bytes each; 8 with four position
-  // tiles, where more spill and 4 measured 182 against 177 us), at most kStreamDepth k-steps, a
-  // power of two that divides the per-chunk step count.  8 waves: one k-step (more measured no
-  // faster).
-  constexpr int D = kWaves == 8 ? 1 : (NT >= 4 ? 8 : 16) / NL;
-  constexpr int Dp = D >= kStreamDepth ? kStreamDepth : (D >= 4 ? 4 : (D >= 2 ? 2 : 1));
+  // tiles, where more spill and 4 measured 182 against 177 us), at most 256 columns, a power of two
+  // that divides the per-chunk step count.  8 waves: one k-step (more measured no faster).
+  constexpr int kLoads = kLines ? NL : (NL + 1) / 2, kMax = kLines ? 4 : 8;
+  constexpr int D = kWaves == 8 ? 1 : (NT >= 4 ? 8 : 16) / kLoads;
+  constexpr int Dp = D >= kMax ? kMax : (D >= 4 ? 4 : (D >= 2 ? 2 : 1));
   const int extra = kAttnD != 0 ? ha.units : 0;
-  hipLaunchKernelGGL((lmhead_stream16_kernel<kWaves, NL, NT, Dp, kTop2, kAttnD>),
+  hipLaunchKernelGGL((lmhead_stream16_kernel<kWaves, NL, NT, Dp, kTop2, kAttnD, kLines>),
                      dim3(pl.groups + extra), dim3(kWaves * 64), 0, s,
                      static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(w), n_rows,
                      hidden, vocab, pl.rows_per_wg, part, part2, pl.groups, ha.p);
   return hipGetLastError();
+}
+
+template <int kWaves, int NL, int NT, bool kTop2, int kAttnD = 0>
+hipError_t launch_stream_nl(int n_rows, int hidden, int vocab, const StreamPlan& pl,
+                            const void* h, const void* w, Partial* part, float* part2,
+                            hipStream_t s, const HostedAttn& ha) {
+  constexpr StreamForm form = kStreamForm<kWaves, NL, NT>;
+  auto go = [&](auto lines) {
+    return launch_stream_form<kWaves, NL, NT, kTop2, kAttnD, lines.value>(
+        n_rows, hidden, vocab, pl, h, w, part, part2, s, ha);
+  };
+  if constexpr (form == kBySize) {
+    if (static_cast<size_t>(vocab) * hidden * 2 <= kStreamLineBytes) return go(std::false_type{});
+  }
+  return go(std::bool_constant<form != kHalfLines>{});
 }
 
 // 16 waves, NL 8-row loads: the variant for the hosted attention's head dimension.
