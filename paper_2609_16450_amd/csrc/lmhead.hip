@@ -688,7 +688,7 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
   constexpr int kInst = kLoadsW ? 2 * TM : 2 * TN;  // 1 KB load instructions per stage
   static_assert(BK == 64, "two 16x16x32 k steps per stage");
   static_assert(Shape::kLdsBytes <= 160 * 1024, "slots fit in LDS");
-  static_assert(BN * (sizeof(Partial) + 4) <= kWSlot, "reduction fits in a W slot");
+  static_assert(WM * BN * (sizeof(Partial) + 4) <= kWSlot, "reduction fits in a W slot");
 
   const int lane = threadIdx.x & 63;
   const int wm = wave % WM, wn = wave / WM;
@@ -819,38 +819,31 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
     if (!pre) wait_vm_lds_and_barrier<0>();  // no DMA in flight
     acc_fence_out(acc);  // every MFMA has written its accumulator before the epilogue reads it
 
-    // Column statistics; the waves of the upper 128 vocabulary rows hand theirs to those of the
-    // lower 128 through the W slot that the last stage left, which is loaded again only in step a
-    // of the next tile's first stage.
-    Partial* red = reinterpret_cast<Partial*>(smem + w2);  // [BN]
-    float* red2 = reinterpret_cast<float*>(red + BN);
+    // Column statistics; the two halves of the vocabulary rows meet through the W slot that the last
+    // stage left, which is loaded again only in step a of the next tile's first stage.
+    Partial* red = reinterpret_cast<Partial*>(smem + w2);  // [WM][BN]
+    float* red2 = reinterpret_cast<float*>(red + WM * BN);
     const bool full = vt * BM + BM <= vocab;
     const int vbase = vt * BM + wm * kWaveM + q4;
-    Partial own[TN];
-    float own2[TN];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
-      own2[tn] = kNegBig;
-      own[tn] = column_stats16<TM, TN, kTop2>(acc, tn, vbase, vocab, full, &own2[tn]);
-      if (wm == 1 && lane < 16) {
-        red[wn * kWaveN + tn * 16 + rho] = own[tn];
-        if (kTop2) red2[wn * kWaveN + tn * 16 + rho] = own2[tn];
+      float m2 = kNegBig;
+      const Partial p = column_stats16<TM, TN, kTop2>(acc, tn, vbase, vocab, full, &m2);
+      if (lane < 16) {
+        red[wm * BN + wn * kWaveN + tn * 16 + rho] = p;
+        if (kTop2) red2[wm * BN + wn * kWaveN + tn * 16 + rho] = m2;
       }
     }
     __syncthreads();
-    if (wm == 0 && lane < 16) {
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) {
-        const int c = wn * kWaveN + tn * 16 + rho;
-        const Partial o = red[c];
-        float m2 = kNegBig;
-        if (kTop2) m2 = top2_merge(own[tn].m, own2[tn], o.m, red2[c]);
-        const Partial p = partial_merge(own[tn], o);
-        const int row = rt * BN + c;
-        if (row < n_rows) {
-          part[static_cast<size_t>(row) * n_vtiles + vt] = p;
-          if (kTop2) part2[static_cast<size_t>(row) * n_vtiles + vt] = m2;
-        }
+    const int c = threadIdx.x;  // one column per thread
+    if (c < BN) {
+      const Partial p = red[c], o = red[BN + c];
+      const int row = rt * BN + c;
+      if (row < n_rows) {
+        part[static_cast<size_t>(row) * n_vtiles + vt] = partial_merge(p, o);
+        if (kTop2)
+          part2[static_cast<size_t>(row) * n_vtiles + vt] =
+              top2_merge(p.m, red2[c], o.m, red2[BN + c]);
       }
     }
     if (!next) break;
