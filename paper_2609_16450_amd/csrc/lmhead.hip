@@ -659,9 +659,7 @@ __device__ __forceinline__ void band_tile(int s, int n_vtiles, int n_rtiles, int
 // while this tile finishes and runs its epilogue.  Measured against 32x32x16 blocks (the
 // same tiles): 16x16x32 MFMAs sustain a higher clock under the chip's power limit.
 //
-// Waves 0 and 1 load W (16 instructions of 1 KB per stage each), waves 2 and 3 load h (2 TN
-// each); the kernel body is instantiated per role (tile_run), because the wait counts are
-// immediates.
+// Every wave loads a quarter of W (8 instructions of 1 KB per stage) and of h (TN).
 constexpr int kTileTM = kTileBM / 32;  // 16-row blocks per wave
 
 template <int TN>
@@ -673,7 +671,7 @@ struct TileShape {
   static constexpr int kLdsBytes = kH0 + 2 * kHSlot;
 };
 
-template <int TN, bool kTop2, bool kLoadsW>
+template <int TN, bool kTop2>
 __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restrict__ h,
                                          const uint16_t* __restrict__ w, int n_rows, int hidden,
                                          int vocab, int n_vtiles, int n_rtiles,
@@ -685,7 +683,7 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
   constexpr int WM = 2, TM = kTileTM;
   constexpr int kWaveM = 16 * TM, kWaveN = 16 * TN;
   constexpr int kReads = TM + TN, kMfmas = TM * TN;
-  constexpr int kInst = kLoadsW ? 2 * TM : 2 * TN;  // 1 KB load instructions per stage
+  constexpr int kWInst = TM, kHInst = TN;  // 1 KB load instructions of this wave per stage
   static_assert(BK == 64, "two 16x16x32 k steps per stage");
   static_assert(Shape::kLdsBytes <= 160 * 1024, "slots fit in LDS");
   static_assert(WM * BN * (sizeof(Partial) + 4) <= kWSlot, "reduction fits in a W slot");
@@ -696,8 +694,8 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
   const int ns = hidden / BK;  // stages per tile, >= 1
   const bool chain = ns >= 2;  // the last stages of a tile load the next tile's first two
 
-  // Load instruction i of this wave covers rows 8 q .. 8 q + 7 of its operand, q = (wave % 2)
-  // kInst + i: eight lanes read 128 contiguous bytes of a row, a whole cache line in one L2 request.
+  // Load instruction i of this wave covers rows 8 q .. 8 q + 7 of W, q = wave kWInst + i, or of h, q =
+  // wave kHInst + i: eight lanes read 128 contiguous bytes of a row, a whole cache line in one L2 request.
   // (16 rows x 64 bytes per instruction make twice the requests, and the L2 request rate then
   // bounds the kernel.)  The loads are buffer loads into LDS, whose range ends with the operand's
   // last row, so rows past the end read as zero without a clamp; tile_loads.hpp has the addresses.
@@ -705,25 +703,35 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
   // same for every second instruction.  (Global loads into LDS would count on the LDS-read counter
   // as well, and the compiler then waits for every outstanding fragment read before each use of
   // one.)
-  const int q0 = (wave & 1) * kInst;
+  const int wq0 = wave * kWInst, hq0 = wave * kHInst;
   const uint32_t row_bytes = static_cast<uint32_t>(hidden) * 2;
-  const uint32_t voff[2] = {tile_load_voff(0, lane, row_bytes), tile_load_voff(1, lane, row_bytes)};
+  uint32_t wvoff[2], hvoff[2];  // by the parity of i
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    wvoff[i] = tile_load_voff((wq0 + i) & 1, lane, row_bytes);
+    hvoff[i] = tile_load_voff((hq0 + i) & 1, lane, row_bytes);
+  }
   struct Src {
-    const uint8_t* base;
-    int rows;  // of the tile inside the operand, > 0
+    const uint8_t *w, *h;
+    int w_rows, h_rows;  // of the tile inside the operands, > 0
   };
   auto source = [&](int vt_, int rt_) {
-    return kLoadsW ? Src{reinterpret_cast<const uint8_t*>(w + static_cast<size_t>(vt_) * BM * hidden),
-                         min(vocab - vt_ * BM, BM)}
-                   : Src{reinterpret_cast<const uint8_t*>(h + static_cast<size_t>(rt_) * BN * hidden),
-                         min(n_rows - rt_ * BN, BN)};
+    return Src{reinterpret_cast<const uint8_t*>(w + static_cast<size_t>(vt_) * BM * hidden),
+               reinterpret_cast<const uint8_t*>(h + static_cast<size_t>(rt_) * BN * hidden),
+               min(vocab - vt_ * BM, BM), min(n_rows - rt_ * BN, BN)};
   };
-  // Load instruction i of stage `stage` of the tile at p, into the slot at `slot`.
-  auto load = [&](const Src& p, int stage, int slot, int i) {
-    const int row0 = tile_load_row0(q0 + i, p.rows);
-    buffer_load_to_lds(make_rsrc(p.base + static_cast<uint32_t>(row0) * row_bytes,
-                                 tile_load_range(row0, p.rows, row_bytes)),
-                       smem + slot + (q0 + i) * 1024, voff[i & 1], stage * (BK * 2));
+  // Load instruction i of W or of h of stage `stage` of the tile at p, into the slot at `slot`.
+  auto load = [&](const uint8_t* base, int rows, int q, uint32_t voff, int stage, int slot) {
+    const int row0 = tile_load_row0(q, rows);
+    buffer_load_to_lds(make_rsrc(base + static_cast<uint32_t>(row0) * row_bytes,
+                                 tile_load_range(row0, rows, row_bytes)),
+                       smem + slot + q * 1024, voff, stage * (BK * 2));
+  };
+  auto load_w = [&](const Src& p, int stage, int slot, int i) {
+    load(p.w, p.w_rows, wq0 + i, wvoff[i & 1], stage, slot);
+  };
+  auto load_h = [&](const Src& p, int stage, int slot, int i) {
+    load(p.h, p.h_rows, hq0 + i, hvoff[i & 1], stage, slot);
   };
   // Fragment f of k step `half` of a stage (f < TM: W block f of this wave, else h block f - TM):
   // lane l reads row rho(l % 16) = 4 (l % 4) + (l % 16) / 4 of the 16-row block, 16-byte chunk
@@ -748,11 +756,15 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
   // Stages 0 and 1 of a tile, then the fragments of (0, a).
   bf16x8 xa[TM], xb[TN], ya[TM], yb[TN];
   auto start = [&]() {
+    auto stage = [&](int st, int wslot, int hslot) {
 #pragma unroll
-    for (int i = 0; i < kInst; ++i) load(src, 0, kLoadsW ? w0 : h0, i);
+      for (int i = 0; i < kWInst; ++i) load_w(src, st, wslot, i);
 #pragma unroll
-    for (int i = 0; i < kInst; ++i) load(src, min(1, ns - 1), kLoadsW ? w1 : h1, i);
-    wait_vm_lds_and_barrier<kInst>();  // stage 0 has landed
+      for (int i = 0; i < kHInst; ++i) load_h(src, st, hslot, i);
+    };
+    stage(0, w0, h0);
+    stage(min(1, ns - 1), w1, h1);
+    wait_vm_lds_and_barrier<kWInst + kHInst>();  // stage 0 has landed
 #pragma unroll
     for (int f = 0; f < TM; ++f) xa[f] = frag(w0, h0, 0, f);
 #pragma unroll
@@ -770,18 +782,18 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
     const bool pre = next && chain;
 
     // One k step: the MFMAs from (ca, cb), the fragments of k step `half` of the stage in slots
-    // wslot / hslot into (na, nb), and with do_load stage `stage` of p into the slot at lslot;
-    // loads and fragment reads spread over the first three quarters of the MFMAs.
-    auto body = [&](int wslot, int hslot, int half, bool do_load, const Src& p, int stage,
-                    int lslot, const bf16x8 (&ca)[TM], const bf16x8 (&cb)[TN],
-                    bf16x8 (&na)[TM], bf16x8 (&nb)[TN]) {
-      auto load_at = [](int l) { return (6 * l + 1) * kMfmas / (8 * kInst); };
+    // wslot / hslot into (na, nb), and the n_loads calls load_one(l); loads and fragment reads spread
+    // over the first three quarters of the MFMAs.
+    auto body = [&](int wslot, int hslot, int half, int n_loads, auto load_one,
+                    const bf16x8 (&ca)[TM], const bf16x8 (&cb)[TN], bf16x8 (&na)[TM],
+                    bf16x8 (&nb)[TN]) {
+      auto load_at = [&](int l) { return (6 * l + 1) * kMfmas / (8 * n_loads); };
       auto read_at = [](int f) { return (6 * (f / 2) + 3 + 2 * (f & 1)) * kMfmas / (4 * kReads); };
       int l = 0, f = 0;  // constants of the unrolled code
 #pragma unroll
       for (int i = 0; i < kMfmas; ++i) {
         mfma16_tied(acc[i / TN][i % TN], ca[i / TN], cb[i % TN]);
-        if (do_load && l < kInst && load_at(l) <= i) load(p, stage, lslot, l++);
+        if (l < n_loads && load_at(l) <= i) load_one(l++);
         if (f < kReads && read_at(f) <= i) {
           if (f < TM)
             na[f] = frag(wslot, hslot, half, f);
@@ -790,14 +802,15 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
           ++f;
         }
       }
-      static_assert(kInst <= kMfmas * 7 / 8, "every load finds its MFMA");
+      static_assert(kWInst <= kMfmas * 7 / 8 && kHInst <= kMfmas * 7 / 8,
+                    "every load finds its MFMA");
     };
     // One stage; stage `stage` of p is loaded on the way.
     auto run_stage = [&](const Src& p, int stage) {
-      body(w0, h0, 1, kLoadsW, p, stage, w2, xa, xb, ya, yb);
-      // the next stage has landed (W: all but the stage just issued)
-      wait_vm_lds_and_barrier<kLoadsW ? kInst : 0>();
-      body(w1, h1, 0, !kLoadsW, p, stage, h0, ya, yb, xa, xb);
+      body(w0, h0, 1, kWInst, [&](int l) { load_w(p, stage, w2, l); }, xa, xb, ya, yb);
+      // the next stage has landed: all but the W loads just issued
+      wait_vm_lds_and_barrier<kWInst>();
+      body(w1, h1, 0, kHInst, [&](int l) { load_h(p, stage, h0, l); }, ya, yb, xa, xb);
       const int w_left = w0, h_left = h0;
       w0 = w1;
       w1 = w2;
@@ -814,7 +827,8 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
     // stage per tile, this tile's last stage again, never read).
     int st = 0;
     for (; st + 2 < ns; ++st) run_stage(src, st + 2);
-    const Src tsrc{pre ? nsrc.base : src.base, pre ? nsrc.rows : src.rows};
+    const Src tsrc{pre ? nsrc.w : src.w, pre ? nsrc.h : src.h, pre ? nsrc.w_rows : src.w_rows,
+                   pre ? nsrc.h_rows : src.h_rows};
     for (; st < ns; ++st) run_stage(tsrc, pre ? st + 2 - ns : ns - 1);
     if (!pre) wait_vm_lds_and_barrier<0>();  // no DMA in flight
     acc_fence_out(acc);  // every MFMA has written its accumulator before the epilogue reads it
@@ -878,12 +892,8 @@ __global__ __launch_bounds__(256, 1) void lmhead_tile_kernel(
   // the wave index is the same on every lane: taken as a scalar, so the LDS destinations of the
   // loads (M0) are scalar arithmetic
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wave < 2)
-    tile_run<TN, kTop2, true>(smem, h, w, n_rows, hidden, vocab, n_vtiles, n_rtiles, part, part2,
-                              s0, step, s_end, wave);
-  else
-    tile_run<TN, kTop2, false>(smem, h, w, n_rows, hidden, vocab, n_vtiles, n_rtiles, part, part2,
-                               s0, step, s_end, wave);
+  tile_run<TN, kTop2>(smem, h, w, n_rows, hidden, vocab, n_vtiles, n_rtiles, part, part2, s0, step,
+                      s_end, wave);
 }
 
 // Tile kernel of the large-batch path: 4 waves, one workgroup per compute unit.  Measured with
