@@ -35,10 +35,11 @@ sys.path.insert(0, ROOT)
 METRIC = "block positions scored+unmasked/sec per denoising step; % HBM or MFMA peak"
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, TFLOP/s
-MFMA_F32_PEAK_TFLOPS = 157.3    # fp32 vector peak (the fp32 path uses plain FMA)
+MFMA_F32_PEAK_TFLOPS = 157.3    # fp32 MFMA peak
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "lmhead_traffic.json")
 LMHEAD_SOURCES = [os.path.join(ROOT, "paper_2609_16450_amd", "csrc", f)
-                  for f in ("lmhead.hip", "eb_common.hpp", "attn_small.hpp", "attn_common.hpp")]
+                  for f in ("lmhead.hip", "eb_common.hpp", "attn_small.hpp", "attn_common.hpp",
+                            "tile_loads.hpp")]
 
 
 def log(msg: str) -> None:
@@ -495,7 +496,8 @@ def ingest_counters(directory: str) -> int:
         "WRITE_SIZE (KiB per dispatch, mean over the dispatches of the run), each scaled by what "
         f"the counter reads for a 1 GiB device-to-device copy: fetch factor "
         f"{factor['FETCH_SIZE']:.4f}, write factor {factor['WRITE_SIZE']:.4f}. source_hash = "
-        "sha256 of the code of lmhead.hip, eb_common.hpp, attn_small.hpp and attn_common.hpp "
+        "sha256 of the code of lmhead.hip, eb_common.hpp, attn_small.hpp, attn_common.hpp and "
+        "tile_loads.hpp "
         "with comments and whitespace removed (first 16 hex digits) when the counters were "
         "taken. Written by `python bench.py --ingest-counters DIR`; commands in "
         "profiles/lmhead_counters.md. For a batch-1 step the launch also runs the step's block "

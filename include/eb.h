@@ -284,8 +284,8 @@ eb_status eb_lbs_select(int32_t n_seq, int32_t window, const uint8_t* masked,
  * merge of the LM-head partials and the unmask run as one epilogue launch (unless a block's
  * rows times the LM head's vocabulary slices exceed 8192, when they run separately; the small
  * steps below always have the one launch; in fp32 that launch computes the attention as well, as
- * long as it has at most 256 tiles of 16 query rows over all sequences and K/V heads and no trace
- * event asks for its time),
+ * long as it has at most 256 tiles of 16 query rows over all sequences and K/V heads, more than 8
+ * (query row, key) pairs per sequence and K/V head, and no trace event asks for its time),
  * and in small bf16 steps (at most 64 block rows, at most 256 query rows per sequence and K/V head,
  * head_dim 64 or 128, an LM head streamed by 16-wave workgroups) the attention's workgroups are
  * queued behind the LM head's in the same launch, which starts them as the LM head's

@@ -661,8 +661,8 @@ __global__ __launch_bounds__(kWaves * 64) void attn_f32_kernel(AttnParamsF32 p) 
   attn_f32_role<D, kWaves * 64, kWaves>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// fp32 attention of a handful of keys and query rows: one wavefront per (block row, query head), its
-// lanes over the head dimension, keys one by one with an online softmax.
+// fp32 attention of a handful of keys and query rows: one wavefront per (block row, query head),
+// its lanes over the head dimension, keys one by one with an online softmax.
 template <int D>
 __global__ __launch_bounds__(64) void attn_f32_row_kernel(AttnParamsF32 p) {
   constexpr int kPer = D / 64;
@@ -705,12 +705,13 @@ __global__ __launch_bounds__(64) void attn_f32_row_kernel(AttnParamsF32 p) {
 
 // Launch of the fp32 attention.
 //  * At most 8 (query row, key) pairs per sequence and K/V head: a wavefront per (row, head).  One
-//    row and 9 keys (head dimension 128): 31 us for 16384 of them against 43 us for MFMA tiles whose
-//    rows and keys are nearly all padding; 4 rows and 4 keys: 58 against 55 us.
+//    row and 9 keys (head dimension 128): 31 us for 16384 of them against 43 us for MFMA tiles
+//    whose rows and keys are nearly all padding; 4 rows and 4 keys: 58 against 55 us.
 //  * At most 128 keys in 1024 or more tiles of query rows: one wave per tile.  There are waves
 //    enough, and eight per tile mostly wait for the merge: one row and 9, 58, 121 keys in 16384
 //    tiles 43, 188, 356 us against 204, 379, 509 us.
-//  * At most 64 keys: four waves, as the others have none (128 tiles of 16 keys: 6.1 against 7.0 us).
+//  * At most 64 keys: four waves, as the others have none (128 tiles of 16 keys: 6.1 against 7.0
+//    us).
 //  * Else eight waves, which also keep few tiles busy.
 hipError_t launch_attn_f32(const AttnArgs& a, int max_keys, hipStream_t s) {
   const AttnParamsF32 p = attn_params_f32(a);

@@ -10,16 +10,17 @@ namespace eb {
 namespace {
 
 // fp32 attention, as the role of a workgroup: a kernel of its own (attn_f32_kernel) or, in a small
-// step, the last workgroups of the epilogue launch, which saves the step a launch.  One workgroup of
-// kWaves wavefronts per (sequence, K/V head, 16 query rows), where the query rows are the (position,
-// head-in-group) pairs.  Wave v takes the 16-key chunks v, v + kWaves, ... of the sequence's keys
-// with an online softmax of its own, and the waves' partial results are merged through LDS.  Scores
-// are formed transposed, S^T = K Q^T, by 16x16x4 fp32 MFMAs (fp32 multiply-adds): lane l owns query
-// l % 16 and holds keys 4 (l / 16) + r of the chunk, which are exactly the k-slots of the B operand
-// of O^T = V^T P^T, one register r per MFMA.  Contraction indices are permuted so that K and Q
-// arrive by 16-byte loads; K and V come straight from global memory (each element is used once per
-// workgroup).  Bound by latency at the sizes this path serves: 32 rows x 4 heads x 64 over 128 keys
-// take 6.3 us, where a wavefront per (row, head) that walked the keys one by one took 61 us.
+// step, the last workgroups of the epilogue launch, which saves the step a launch.  One workgroup
+// of kWaves wavefronts per (sequence, K/V head, 16 query rows), where the query rows are the
+// (position, head-in-group) pairs.  Wave v takes the 16-key chunks v, v + kWaves, ... of the
+// sequence's keys with an online softmax of its own, and the waves' partial results are merged
+// through LDS.  Scores are formed transposed, S^T = K Q^T, by 16x16x4 fp32 MFMAs (fp32
+// multiply-adds): lane l owns query l % 16 and holds keys 4 (l / 16) + r of the chunk, which are
+// exactly the k-slots of the B operand of O^T = V^T P^T, one register r per MFMA.  Contraction
+// indices are permuted so that K and Q arrive by 16-byte loads; K and V come straight from global
+// memory (each element is used once per workgroup).  Bound by latency at the sizes this path
+// serves: 32 rows x 4 heads x 64 over 128 keys take 6.3 us, where a wavefront per (row, head) that
+// walked the keys one by one took 61 us.
 struct AttnParamsF32 {
   const int32_t* cu_block;
   const int32_t* cu_prefix;

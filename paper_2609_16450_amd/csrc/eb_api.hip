@@ -413,8 +413,8 @@ eb_status eb_unmask_select_topm(const eb_ragged* r, const float* conf, const int
   if (m < 0) return fail(EB_ERR_INVALID, "m must be >= 0 (got %d)", m);
   st = check_device(r, false, tau, stream);
   if (st != EB_OK) return st;
-  return hip_status(eb::unmask_select_topm(r->batch, r->max_block, r->cu_block, conf, argmax, tau, m, masked,
-                                           tokens, unmask, n_commit, resolved, stream),
+  return hip_status(eb::unmask_select_topm(r->batch, r->max_block, r->cu_block, conf, argmax, tau,
+                                           m, masked, tokens, unmask, n_commit, resolved, stream),
                     "eb_unmask_select_topm launch");
 }
 

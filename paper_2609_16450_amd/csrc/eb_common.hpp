@@ -60,12 +60,12 @@ __device__ __forceinline__ float sum2_bf16(uint32_t w, float acc) {
 }
 
 // Buffer loads straight into LDS.  A raw buffer resource over `bytes` bytes of memory starting at
-// `base` (word 3 as gfx9 raw dword loads need; loads past the range return zeros); 16 bytes per lane from byte offset voff + soff
-// into LDS at l + 16 * lane (the LDS address is wave-uniform).  The builtins sit in device
-// functions of their own: inside a kernel body the host compilation would drop the kernel.
-// (Loads into LDS issued as global loads count on the LDS-read counter as well, and the
-// compiler then waits for every outstanding LDS read before each use of one; buffer loads do
-// not.)
+// `base` (word 3 as gfx9 raw dword loads need; loads past the range return zeros); 16 bytes per
+// lane from byte offset voff + soff into LDS at l + 16 * lane (the LDS address is wave-uniform).
+// The builtins sit in device functions of their own: inside a kernel body the host compilation
+// would drop the kernel. (Loads into LDS issued as global loads count on the LDS-read counter as
+// well, and the compiler then waits for every outstanding LDS read before each use of one; buffer
+// loads do not.)
 typedef __attribute__((address_space(3))) void lds_void_t;
 constexpr int kBufferWord3 = 0x00020000;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base,

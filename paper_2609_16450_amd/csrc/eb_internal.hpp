@@ -82,20 +82,20 @@ hipError_t lps_features(int batch, const int32_t* cu_block, int vocab, const flo
                         hipStream_t s);
 
 // ---- fused step epilogue ---------------------------------------------------------------
-// One launch after lmhead_partials and block_attn(..., defer_merge = true): merges the attention key
-// splits, combines each row's LM-head partials into conf / entropy / argmax / max_logit, and applies
-// the threshold unmask per block.  With attn_f32 it also computes the attention of an fp32 step,
-// which then needs no block_attn (step_finish_hosts_attn says when that pays).  Taken while one
-// workgroup reduces a block's partials quickly (max_block * n_slices <= kFinishMaxPartials); a
+// One launch after lmhead_partials and block_attn(..., defer_merge = true): merges the attention
+// key splits, combines each row's LM-head partials into conf / entropy / argmax / max_logit, and
+// applies the threshold unmask per block.  With attn_f32 it also computes the attention of an fp32
+// step, which then needs no block_attn (step_finish_hosts_attn says when that pays).  Taken while
+// one workgroup reduces a block's partials quickly (max_block * n_slices <= kFinishMaxPartials); a
 // larger block's partials keep one compute unit busy longer than the separate kernels take, which
 // spread the rows over all of them (whole steps, fused against separate: 217.5 against 211 us with
-// 32 x 494 partials per block, 239 against 208 us with 128 x 494).  A hosted attention's split merge
-// needs it: see lmhead_hosts_attn.
+// 32 x 494 partials per block, 239 against 208 us with 128 x 494).  A hosted attention's split
+// merge needs it: see lmhead_hosts_attn.
 constexpr long kFinishMaxPartials = 1L << 13;
 bool step_finish_fusable(int max_block, int n_slices);
 bool step_finish_hosts_attn(bool bf16, const AttnArgs& a);
-hipError_t step_finish(bool bf16, bool attn_f32, const AttnArgs& a, void* attn_ws, int n_rows, int vocab,
-                       const void* lm_ws, float* conf, float* entropy, int32_t* argmax,
+hipError_t step_finish(bool bf16, bool attn_f32, const AttnArgs& a, void* attn_ws, int n_rows,
+                       int vocab, const void* lm_ws, float* conf, float* entropy, int32_t* argmax,
                        float* max_logit, const float* tau, uint8_t* masked, int32_t* tokens,
                        uint8_t* unmask, int32_t* n_commit, uint8_t* resolved, hipStream_t s);
 

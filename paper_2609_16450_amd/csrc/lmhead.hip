@@ -45,9 +45,9 @@ constexpr int kStreamGroups = EB_STREAM_GROUPS;  // workgroups (256: one per com
 //    load.
 //  * Whole lines (kLines): a k-step is 64 columns of a 16-row tile in two loads of 8 rows x 128
 //    bytes: lane l loads 16-byte chunk line_chunk(l) of row l % 8 (v0) and of row 8 + l % 8 (v1).
-//    line_to_frag exchanges v0 and v1 between lanes l and l ^ 8, after which lane l holds row l % 16
-//    in both, chunk l / 16 in the first and 4 + l / 16 in the second: the A operands of the MFMAs of
-//    the step's first and last 32 columns.
+//    line_to_frag exchanges v0 and v1 between lanes l and l ^ 8, after which lane l holds row l %
+//    16 in both, chunk l / 16 in the first and 4 + l / 16 in the second: the A operands of the
+//    MFMAs of the step's first and last 32 columns.
 // Either way a logit is summed in the order of its columns, as in the tile kernel, so a position's
 // logits do not depend on how many positions the call has.
 __device__ __forceinline__ int line_chunk(int lane) { return (lane >> 4) + 4 * ((lane >> 3) & 1); }
@@ -79,8 +79,8 @@ __device__ __forceinline__ float top2_shfl_merge(float m, float m2, int mask) {
 // Statistics of column l % 16 of position tile nt of a wave's natural-order 16x16 accumulator
 // tiles, whose rows are vocabulary entries wb + 16 tm + 4 (l / 16) + r below we: per lane, then
 // merged over the column's four lanes in a canonical order.  With kTop2, m2 is the second-largest
-// logit (kNegBig if none).  With kAnyLogit, logits of -inf (and NaN) add nothing, instead of the NaN
-// that 0 * -inf makes of t; no other result changes.
+// logit (kNegBig if none).  With kAnyLogit, logits of -inf (and NaN) add nothing, instead of the
+// NaN that 0 * -inf makes of t; no other result changes.
 template <int TM, int NT, bool kTop2, bool kAnyLogit = false>
 __device__ __forceinline__ Partial wave_column_stats(const f32x4 (&acc)[TM][NT], int nt, int wb,
                                                      int we, int lane, float& m2) {
@@ -345,12 +345,12 @@ struct HostedAttn {
 // Whole lines or half lines per load.  Half lines make the shorter k-step, so the loop runs closer
 // to its loads; whole lines make half the requests.  With three or more 8-row shares per wave what
 // decides is whether W fits the 256 MB cache in front of HBM, where a program that calls the head
-// again and again finds it: whole lines take 2 to 5% longer up to 260 MB (100000 x 1024: 37.3 -> 38.9
-// us for one position, 41.2 -> 43.0 us for 64) and 2 to 8% less above 300 MB (126464 x 4096: 193.7 ->
-// 183.1 us, 195.4 -> 189.0 us).  With two, half lines are never behind (65536 x 2048: 42.8 against
-// 48.6 us for one position; x 4096: 110.7 against 112.9 us).  With one, whole lines read 8 rows
-// instead of 16 (8192 x 2048: 16.5 -> 13.9 us), except that with four position tiles there is nothing
-// to gain (24000 x 4096, 64 positions: 45.4 -> 48.7 us).
+// again and again finds it: whole lines take 2 to 5% longer up to 260 MB (100000 x 1024: 37.3 ->
+// 38.9 us for one position, 41.2 -> 43.0 us for 64) and 2 to 8% less above 300 MB (126464 x 4096:
+// 193.7 -> 183.1 us, 195.4 -> 189.0 us).  With two, half lines are never behind (65536 x 2048: 42.8
+// against 48.6 us for one position; x 4096: 110.7 against 112.9 us).  With one, whole lines read 8
+// rows instead of 16 (8192 x 2048: 16.5 -> 13.9 us), except that with four position tiles there is
+// nothing to gain (24000 x 4096, 64 positions: 45.4 -> 48.7 us).
 constexpr size_t kStreamLineBytes = 280u << 20;
 enum StreamForm { kHalfLines, kWholeLines, kBySize };
 template <int kWaves, int NL, int NT>
@@ -362,9 +362,10 @@ template <int kWaves, int NL, int NT, bool kTop2, int kAttnD, bool kLines>
 hipError_t launch_stream_form(int n_rows, int hidden, int vocab, const StreamPlan& pl,
                               const void* h, const void* w, Partial* part, float* part2,
                               hipStream_t s, const HostedAttn& ha) {
-  // 16 waves: up to 16 W registers in flight per lane (16 bytes each; 8 with four position
-  // tiles, where more spill and 4 measured 182 against 177 us), at most 256 columns, a power of two
-  // that divides the per-chunk step count.  8 waves: one k-step (more measured no faster).
+  // 16 waves: up to 16 W registers in flight per lane (16 bytes each; 8 with four position tiles,
+  // where more spill and 4 measured 182 against 177 us; five and six shares spill 3 to 5 registers
+  // all the same), at most 256 columns, a power of two that divides the per-chunk step count.  8
+  // waves: one k-step (more measured no faster).
   constexpr int kLoads = kLines ? NL : (NL + 1) / 2, kMax = kLines ? 4 : 8;
   constexpr int D = kWaves == 8 ? 1 : (NT >= 4 ? 8 : 16) / kLoads;
   constexpr int Dp = D >= kMax ? kMax : (D >= 4 ? 4 : (D >= 2 ? 2 : 1));
@@ -550,13 +551,13 @@ __device__ __forceinline__ void pair_sum_min(float& s, float& t, int32_t& idx) {
 // Statistics of one column of a wave's 16x16x32 accumulator tile: lane l holds, for column block
 // tn, vocabulary rows vbase + 16 tm + 4 r (tm < TM, r < 4; vbase includes the lane's l / 16) of
 // one column, and the four lanes l % 16 + 16 q together hold the column's 16 TM rows (the rows
-// of a 16-row block reach the MFMA in the order the fragment reads use, see tile_run).  A max pass in four chains (by r), the column maximum M over the four
-// lanes (pair_max), one exponential pass against M, then the four lanes' sums added pairwise in
-// registers (pair_sum_min): identical bits on all four lanes.  Each chain walks its rows in
-// decreasing order, so its last z == M is its lowest row; the argmax is kept as the block index
-// tm, a constant of the unrolled code.  kFull (every row inside the vocabulary) drops the
-// per-row bounds test.  With kTop2, m2 returns the column's second-largest logit (kNegBig if
-// none).
+// of a 16-row block reach the MFMA in the order the fragment reads use, see tile_run).  A max pass
+// in four chains (by r), the column maximum M over the four lanes (pair_max), one exponential pass
+// against M, then the four lanes' sums added pairwise in registers (pair_sum_min): identical bits
+// on all four lanes.  Each chain walks its rows in decreasing order, so its last z == M is its
+// lowest row; the argmax is kept as the block index tm, a constant of the unrolled code.  kFull
+// (every row inside the vocabulary) drops the per-row bounds test.  With kTop2, m2 returns the
+// column's second-largest logit (kNegBig if none).
 template <int TM, int TN, bool kTop2, bool kFull>
 __device__ __forceinline__ Partial column_stats16(const f32x4 (&acc)[TM][TN], int tn, int vbase,
                                                   int vocab, float* m2) {
@@ -694,15 +695,15 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
   const int ns = hidden / BK;  // stages per tile, >= 1
   const bool chain = ns >= 2;  // the last stages of a tile load the next tile's first two
 
-  // Load instruction i of this wave covers rows 8 q .. 8 q + 7 of W, q = wave kWInst + i, or of h, q =
-  // wave kHInst + i: eight lanes read 128 contiguous bytes of a row, a whole cache line in one L2 request.
-  // (16 rows x 64 bytes per instruction make twice the requests, and the L2 request rate then
-  // bounds the kernel.)  The loads are buffer loads into LDS, whose range ends with the operand's
-  // last row, so rows past the end read as zero without a clamp; tile_loads.hpp has the addresses.
-  // The resource of a 16-row group is scalar arithmetic on the tile's base; the vector offset is the
-  // same for every second instruction.  (Global loads into LDS would count on the LDS-read counter
-  // as well, and the compiler then waits for every outstanding fragment read before each use of
-  // one.)
+  // Load instruction i of this wave covers rows 8 q .. 8 q + 7 of W, q = wave kWInst + i, or of h,
+  // q = wave kHInst + i: eight lanes read 128 contiguous bytes of a row, a whole cache line in one
+  // L2 request. (16 rows x 64 bytes per instruction make twice the requests, and the L2 request
+  // rate then bounds the kernel.)  The loads are buffer loads into LDS, whose range ends with the
+  // operand's last row, so rows past the end read as zero without a clamp; tile_loads.hpp has the
+  // addresses. The resource of a 16-row group is scalar arithmetic on the tile's base; the vector
+  // offset is the same for every second instruction.  (Global loads into LDS would count on the
+  // LDS-read counter as well, and the compiler then waits for every outstanding fragment read
+  // before each use of one.)
   const int wq0 = wave * kWInst, hq0 = wave * kHInst;
   const uint32_t row_bytes = static_cast<uint32_t>(hidden) * 2;
   uint32_t wvoff[2], hvoff[2];  // by the parity of i
@@ -782,8 +783,8 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
     const bool pre = next && chain;
 
     // One k step: the MFMAs from (ca, cb), the fragments of k step `half` of the stage in slots
-    // wslot / hslot into (na, nb), and the n_loads calls load_one(l); loads and fragment reads spread
-    // over the first three quarters of the MFMAs.
+    // wslot / hslot into (na, nb), and the n_loads calls load_one(l); loads and fragment reads
+    // spread over the first three quarters of the MFMAs.
     auto body = [&](int wslot, int hslot, int half, int n_loads, auto load_one,
                     const bf16x8 (&ca)[TM], const bf16x8 (&cb)[TN], bf16x8 (&na)[TM],
                     bf16x8 (&nb)[TN]) {
@@ -833,8 +834,8 @@ __device__ __forceinline__ void tile_run(uint8_t* smem, const uint16_t* __restri
     if (!pre) wait_vm_lds_and_barrier<0>();  // no DMA in flight
     acc_fence_out(acc);  // every MFMA has written its accumulator before the epilogue reads it
 
-    // Column statistics; the two halves of the vocabulary rows meet through the W slot that the last
-    // stage left, which is loaded again only in step a of the next tile's first stage.
+    // Column statistics; the two halves of the vocabulary rows meet through the W slot that the
+    // last stage left, which is loaded again only in step a of the next tile's first stage.
     Partial* red = reinterpret_cast<Partial*>(smem + w2);  // [WM][BN]
     float* red2 = reinterpret_cast<float*>(red + WM * BN);
     const bool full = vt * BM + BM <= vocab;
@@ -896,9 +897,10 @@ __global__ __launch_bounds__(256, 1) void lmhead_tile_kernel(
                       s_end, wave);
 }
 
-// Tile kernel of the large-batch path: 4 waves, one workgroup per compute unit.  Measured with
-// 1024 positions of a 126464 x 4096 head: 807 us, against 945 us with stages of 32 columns (64
-// contiguous bytes per row and load: twice the L2 requests); 4096 positions: 3.03 against 3.46 ms.
+// Tile kernel of the large-batch path: 4 waves, one workgroup per compute unit.  1000 positions of a
+// 126464 x 4096 head take 768 us, against 900 us with stages of 32 columns (64 contiguous bytes per
+// row and load: twice the L2 requests), 2048 positions of 126464 x 2048 811 against 949 us.  With two
+// waves loading W and two loading h, and the body once per role, it was 781 and 827 us.
 // Measured and dropped (with 32x32x16 blocks): 8 waves of 128 x 64 (10.55 ms), 256 x 128 tiles
 // with a ring of 3 at two workgroups per compute unit (11.8 ms), stages reaching LDS through
 // registers (9.65 ms), 384 x 256 tiles (384 accumulators per lane: the compiler spills).
@@ -1150,8 +1152,8 @@ size_t lmhead_ws_bytes(bool bf16, int n_rows, int vocab, bool top2) {
     if (top2) b += static_cast<size_t>(rows) * lmhead_num_slices(bf16, rows, vocab) * 4;
     return b;
   };
-  // fp32: also enough for every smaller row count, whose slices may be four times as many, so that a
-  // workspace made for the largest call serves the others
+  // fp32: also enough for every smaller row count, whose slices may be four times as many, so that
+  // a workspace made for the largest call serves the others
   return bf16 ? bytes(n_rows)
               : max(bytes(n_rows), bytes(min(n_rows, f32_small_slice_rows(vocab))));
 }

@@ -120,13 +120,14 @@ bool step_finish_fusable(int max_block, int n_slices) {
 // its own, one of 256 attention workgroups over 320 to 4000 keys 3 to 27% less.  A workgroup here
 // has twice the waves that the attention needs and fills a compute unit, which holds two of the
 // attention kernel's own: 512 to 2048 workgroups took 45 against 42 us, 270 against 190 us and 1239
-// against 793 us (head dimension 128), at 64 up to a fifth more.
+// against 793 us (head dimension 128), at 64 up to a fifth more.  A handful of (row, key) pairs has
+// a kernel of its own.
 bool step_finish_hosts_attn(bool bf16, const AttnArgs& a) {
   return !bf16 && a.total_block > 0 && attn_f32_groups(a) <= 256 && !attn_f32_few(a);
 }
 
-hipError_t step_finish(bool bf16, bool attn_f32, const AttnArgs& a, void* attn_ws, int n_rows, int vocab,
-                       const void* lm_ws, float* conf, float* entropy, int32_t* argmax,
+hipError_t step_finish(bool bf16, bool attn_f32, const AttnArgs& a, void* attn_ws, int n_rows,
+                       int vocab, const void* lm_ws, float* conf, float* entropy, int32_t* argmax,
                        float* max_logit, const float* tau, uint8_t* masked, int32_t* tokens,
                        uint8_t* unmask, int32_t* n_commit, uint8_t* resolved, hipStream_t s) {
   SplitPlan sp{1, 0};

@@ -17,8 +17,8 @@ namespace eb {
 // as the offset is less than a row) or not (then a lane past the operand's last row is out of range
 // by its vector offset alone).  Loads out of range return zeros.
 
-// First row of the resource of instruction q: the 16-row group of its rows, or for a group that lies
-// past the operand the last one that does not (those rows' logits are used by nobody).
+// First row of the resource of instruction q: the 16-row group of its rows, or for a group that
+// lies past the operand the last one that does not (those rows' logits are used by nobody).
 constexpr int tile_load_row0(int q, int rows) {
   const int group = (q & ~1) * 8, last = (rows - 1) & ~15;
   return group < last ? group : last;

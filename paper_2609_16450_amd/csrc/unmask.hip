@@ -211,9 +211,9 @@ hipError_t unmask_select_topm(int batch, int max_block, const int32_t* cu_block,
                          n_commit, resolved, s);
   // The fewest threads that rank a whole block in one round, up to 1024: a barrier costs less with
   // fewer waves, and small workgroups share a compute unit.  With the copy that refills the mask
-  // flags, 32768 blocks of one row take 25 us with 64 threads, 290 us with 1024; 64 blocks of 16, 64
-  // and 128 rows 6.3, 7.4 and 8.5 us with one round of 64, 256 and 512 threads, 7.6, 8.4 and 9.1 us
-  // with 1024, and with two rounds 7.6 (32 rows by 64 threads) and 10.5 us (128 by 256).
+  // flags, 32768 blocks of one row take 25 us with 64 threads, 290 us with 1024; 64 blocks of 16,
+  // 64 and 128 rows 6.3, 7.4 and 8.5 us with one round of 64, 256 and 512 threads, 7.6, 8.4 and 9.1
+  // us with 1024, and with two rounds 7.6 (32 rows by 64 threads) and 10.5 us (128 by 256).
   auto go = [&](auto kernel, int threads) {
     hipLaunchKernelGGL(kernel, dim3(batch), dim3(threads), 0, s, cu_block, conf, argmax, tau, m,
                        masked, tokens, unmask, n_commit, resolved);

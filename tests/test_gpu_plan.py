@@ -53,11 +53,11 @@ def test_epilogue_rule(rows, vocab):
         assert torch.equal(getattr(a, k), getattr(b, k)), k
 
 
-# fp32 steps, bit for bit against the separate entry points.  The attention is in the epilogue launch
-# with up to 256 workgroups (tiles of 16 query rows, K/V heads, sequences), when that is one launch:
-# 70001 entries are 274 slices, so a block of 29 rows has 7946 partials (one launch) and one of 30
-# rows 8220 (three kernels).  Empty blocks, both head dimensions in the epilogue, and a step of four
-# (row, key) pairs, whose attention is a launch of its own.
+# fp32 steps, bit for bit against the separate entry points.  The attention is in the epilogue
+# launch with up to 256 workgroups (tiles of 16 query rows, K/V heads, sequences), when that is one
+# launch: 70001 entries are 274 slices, so a block of 29 rows has 7946 partials (one launch) and one
+# of 30 rows 8220 (three kernels).  Empty blocks, both head dimensions in the epilogue, and a step
+# of four (row, key) pairs, whose attention is a launch of its own.
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("lens,hq,hkv,vocab", [
     ((20, 0, 7, 33), 4, 2, 2048), ((0, 1, 5, 0), 3, 1, 300),
