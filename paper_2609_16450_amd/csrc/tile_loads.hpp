@@ -29,9 +29,9 @@ constexpr uint32_t tile_load_range(int row0, int rows, uint32_t row_bytes) {
   return static_cast<uint32_t>(rows - row0) * row_bytes;
 }
 
-// 16-byte chunk c of row r sits at place c ^ tile_swizzle(r) of the LDS row of eight places.  LDS has
-// 16 places of 16 bytes across its banks and serves 32 lanes of a fragment read in two parts (lanes
-// 0-3, 12-15 and 20-27, then the others): with this order every read is a 2-way conflict
+// 16-byte chunk c of row r sits at place c ^ tile_swizzle(r) of the LDS row of eight places.  LDS
+// has 16 places of 16 bytes across its banks and serves 32 lanes of a fragment read in two parts
+// (lanes 0-3, 12-15 and 20-27, then the others): with this order every read is a 2-way conflict
 // (SQ_LDS_BANK_CONFLICT 6.5e8 in a launch with 1.6e8 reads of 4 cycles each).  It hides behind the
 // MFMAs.  With row bit 1 in the place of bit 0 no read has a conflict (1.4e6 counted), and 1024
 // positions of a 126464 x 4096 head take 768 us both ways, 9626 of 152064 x 3584 7323 and 7340 us,
