@@ -47,8 +47,9 @@ def test_tile_edges(rows, hidden):
 @pytest.mark.parametrize("vocab", [1, 40, 30000, 40000, 70000, 100001, 152064, 190000])
 def test_stream_loads(rows, hidden, vocab):
     """LM-head streaming kernel: one to six 8-row loads per wave (with whole and half 16-row tiles
-    and waves without rows), one, two and four position tiles, hidden sizes of one k-step, of less
-    than a chunk and of a chunk and a remainder."""
+    and waves without rows), one, two and four position tiles, hidden sizes of one 64-column k-step,
+    of less than a chunk and of a chunk and a remainder; whole lines with one load and, at the
+    largest hidden size, with five and six, half lines otherwise."""
     print(f"stream rows={rows} hidden={hidden} vocab={vocab}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(rows + 100 * hidden + vocab)
     w = torch.randn(vocab, hidden, generator=g, device="cuda").mul_(hidden ** -0.5).bfloat16()
